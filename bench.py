@@ -189,13 +189,14 @@ def traffic_for(kernel: str, launches_bytes: float):
 
 
 FINE_KERNELS = {  # finest-level FP64 pass symbols -> kernel class
-    "k_pass_fine<double, 2, 1, true, true>": "fine_down",
-    "k_pass_fine<double, 2, 1, true, false>": "fine_down",
-    "k_pass_fine<double, 2, 1, false, false>": "fine_up",
+    # from the Dirichlet ring around a zero interior, and from an iterate
+    "k_pass_fine<double, 2, 1, true, 0>": "fine_down",
+    "k_pass_fine<double, 2, 2, true, 0>": "fine_down",
+    "k_pass_fine<double, 2, 4, true, 0>": "fine_up",
     # the first down pass after the full-multigrid start (forms the start itself)
-    "k_pass_fine_pro<double, 2, 1>": "fine_down_pro",
+    "k_pass_fine<double, 2, 3, true, 0>": "fine_down_pro",
     # the up pass of one cycle and the down pass of the next
-    "k_pass_merge<double, 4, 1>": "fine_merged",
+    "k_pass_merge<double, 4, true, 0>": "fine_merged",
 }
 
 

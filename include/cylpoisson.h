@@ -178,8 +178,10 @@ void cylpoisson_plan_destroy(cylpoisson_plan* plan);
  *   "fused"          1 = fused streaming passes (all sweeps, residual and grid
  *                    transfer of a level in one kernel), 0 = one kernel per
  *                    sweep everywhere (default 1)
- *   "chunk_rows"     axial rows per workgroup of the fused passes (0 = automatic)
- *   "prefetch"       rows the fused passes load ahead of the one they consume (1 .. 3; default 1)
+ *   "chunk_rows"     axial rows per wavefront of the finest level's fused passes (0 =
+ *                    automatic: as many chunks as keep every wavefront resident)
+ *   "prefetch"       accepted and read back, without effect: the fused passes load
+ *                    two rows ahead of the one they consume (1 .. 3; default 1)
  *   "timing"         1 = record per-kernel-class device times (cylpoisson_stats);
  *                    2 = the finest-level pass classes only (fewer event records
  *                    between the other launches); 0 = off (0 .. 2; default 0)
@@ -260,10 +262,10 @@ void cylpoisson_plan_destroy(cylpoisson_plan* plan);
  *                    iterates and answers are bitwise those of separate passes;
  *                    such a cycle's residual norm is not formed (NaN in the
  *                    history).  Applies with the fused passes on the finest level,
- *                    nu1 + nu2 from 4 to 6, at most 512 radial nodes and one
+ *                    nu1 + nu2 from 4 to 6, at most 513 radial nodes and one
  *                    plane group; captured graphs ("graph") merge the same
  *                    passes (default 1)
- *   "merge_prefetch" rows the merged pass loads ahead of the one it consumes (1 .. 2; default 1)
+ *   "merge_prefetch" accepted and read back, without effect, as "prefetch" (1 .. 2; default 1)
  *   "direct"         exact solve of a coarse level (Sec. 3.3 solves the coarsest one
  *                    directly): the V-cycle stops at that level and solves it on every
  *                    plane with the axial generalised eigenvectors of the level's
@@ -296,8 +298,8 @@ int cylpoisson_plan_get_option(const cylpoisson_plan* plan, const char* key, dou
 /* Autotuner for the launch shapes of the fused passes: times short solves (two
  * V-cycles, synthetic charge in two temporary node arrays it allocates and
  * frees) on `stream`, varying one option at a time over candidate values of
- * "chunk_rows", "chunk_rows_coarse", "prefetch" and "groups", and keeps a value
- * only when it is at least 3% faster.  Leaves those four options at the chosen
+ * "chunk_rows", "chunk_rows_coarse" and "groups", and keeps a value
+ * only when it is at least 3% faster.  Leaves those three options at the chosen
  * values (read them with cylpoisson_plan_get_option) and every other option as
  * it was.  Results of later solves do not depend on the choice beyond rounding
  * order (tile shapes do not change the arithmetic of a node).  With option

@@ -78,7 +78,6 @@ int cylpoisson_autotune(cylpoisson_plan* p, void* stream) {
     std::vector<Candidate> cands = {
         {"chunk_rows", {0, 32, 48, 64, 96, 128, 192, 256}},
         {"chunk_rows_coarse", {0, 16, 24, 32, 48, 64}},
-        {"prefetch", {1, 2, 3}},
         {"groups", {1, 2, 4}},
     };
     double best = INFINITY;
@@ -148,7 +147,6 @@ int cylpoisson_autotune(cylpoisson_plan* p, void* stream) {
     p->opt = saved;
     p->opt.chunk_rows = tuned.chunk_rows;
     p->opt.chunk_rows_coarse = tuned.chunk_rows_coarse;
-    p->opt.prefetch = tuned.prefetch;
     p->opt.groups = tuned.groups;
     if (status == CYLPOISSON_OK) p->opt.omega = omega;
     drop_graphs(p);

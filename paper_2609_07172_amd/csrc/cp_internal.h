@@ -61,9 +61,6 @@ struct DeviceLevel {
     double* f = nullptr;
     double* r = nullptr;  // residual scratch (ring kept at zero)
     double* u2 = nullptr; // second iterate buffer for the fused kernels
-    // fused-pass tables (towards the next coarser level)
-    const int* colc = nullptr;             // fine column -> coincident coarse interior column or -1
-    const int* rowc = nullptr;             // fine row -> coincident coarse interior row or -1
     // rows reg_lo <= k < reg_hi share the axial coefficients (zc0, zs0, zn0);
     // the rows outside that band are irregular (uneven spacing near the faces
     // or everywhere on a stretched mesh)
@@ -107,9 +104,9 @@ struct Options {
     int max_cycles = 40;
     int check_every = 1;
     int fused = 1;
-    int chunk_rows = 0;  // rows per workgroup in the finest fused passes (0 = automatic)
+    int chunk_rows = 0;  // rows per wavefront in the finest fused passes (0 = automatic)
     int chunk_rows_coarse = 0;  // the same on the coarser levels
-    int prefetch = 1;    // rows the fused passes load ahead of the row they consume
+    int prefetch = 1;    // kept for callers that set it; the passes load two rows ahead
     int timing = 0;      // record per-kernel-class device times with HIP events
     int bottom = 1;      // run the small levels in one LDS-resident kernel per plane
     int fft = 1;         // azimuthal transforms as register FFTs where Ntheta allows
@@ -128,8 +125,8 @@ struct Options {
     int nu1_coarse = 0, nu2_coarse = 0;  // sweeps on levels >= 1 (0: nu1, nu2)
     int fmg = 0;           // 1: full-multigrid start before the V-cycles
     int merge = 1;         // 1: merged finest pass between cycles without a convergence check
-    int merge_prefetch = 1;  // rows the merged finest pass loads ahead (1 or 2)
-    int chunk_rows_merge = 0;  // axial rows per workgroup of the merged pass (0 = automatic)
+    int merge_prefetch = 1;  // likewise
+    int chunk_rows_merge = 0;  // axial rows per wavefront of the merged pass (0 = automatic)
     int tune_omega = 0;    // 1: cylpoisson_autotune also picks omega by the measured contraction
     int nn_target = 0;     // training targets: 0 = SOR correction of the residual, 1 = V-cycle iterate error
     int direct = 1;        // exact separable solve of a coarse level, where the V-cycles stop:
@@ -391,8 +388,6 @@ bool direct_active(const cylpoisson_plan* p);
 hipError_t launch_direct(cylpoisson_plan* p, hipStream_t s, int p0 = 0, int np = -1);
 
 // ---- fused passes (fused.hip) ----
-// the LDS limits of the fused kernels (once per device, when a plan is built)
-hipError_t fused_prepare();
 bool fused_supported(const cylpoisson_plan* p, int l);
 // The LDS bottom kernel serves the small levels (options bottom, fused, point smoother).
 bool bottom_active(const cylpoisson_plan* p);

@@ -196,7 +196,8 @@ bool invert(std::vector<double>& a, int n, std::vector<double>& inv) {
 template <typename T>
 hipError_t dev_alloc(cylpoisson_plan* p, T** out, size_t count) {
     void* ptr = nullptr;
-    const size_t bytes = std::max<size_t>(count, 1) * sizeof(T);
+    // the fused passes load column pairs, the last one of a row with the value after it
+    const size_t bytes = std::max<size_t>(count, 1) * sizeof(T) + 2 * sizeof(double);
     hipError_t e = hipMalloc(&ptr, bytes);
     if (e != hipSuccess) return e;
     p->allocations.push_back(ptr);
@@ -408,10 +409,52 @@ bool bottom_active(const cylpoisson_plan* p) {
     return p->opt.bottom && p->opt.fused && p->opt.smoother == 0;
 }
 
+namespace {
+
+// The sizes that mixed precision, masks and plane groups are offered for: a
+// level coarsened in r, whose rows' pipeline of nu sweeps (one to two rows of
+// prefetch) and per-row tables fit in 64 KB of LDS (80 KB on a stretched mesh)
+// in FP64.  The passes no longer need LDS, but what these options accept and
+// refuse stays as it was.
+bool offered_level(const cylpoisson_plan* p, int l) {
+    const DeviceLevel& L = p->dl[l];
+    const DeviceLevel& C = p->dl[l + 1];
+    const int tn = L.v.nr / 2, rows = L.v.nz - 2;
+    if (tn < 1 || tn > 512 || C.v.nr - 2 > tn) return false;
+    bool stretched = false;
+    size_t most = 0;
+    for (int down = 0; down < 2; ++down) {
+        const int nu = down ? nu_pre(p, l) : nu_post(p, l);
+        int chunk = l == 0 ? p->opt.chunk_rows : p->opt.chunk_rows_coarse;
+        if (chunk <= 0 && l == 0) {
+            const int per_plane = std::max(1, 512 / std::max(1, p->nt));
+            chunk = std::max(64, (rows + per_plane - 1) / per_plane);
+        } else if (chunk <= 0) {
+            const int waves = (tn + 63) / 64;
+            const int per_plane = std::min(kMaxPartial, std::max(1, (2048 + p->nt * waves - 1) / (p->nt * waves)));
+            chunk = std::max(8, (rows + per_plane - 1) / per_plane);
+        }
+        chunk = std::min(std::max(chunk, 1), std::max(rows, 1));
+        if ((rows + chunk - 1) / chunk > kMaxPartial) return false;
+        const int pd = nu == 2 ? p->opt.prefetch : 2;
+        const bool st = 2 * (L.reg_hi - L.reg_lo) < L.v.nz - 2 && pd == 1 && nu == 2;
+        const int q0 = 2 * nu + 3 + pd;
+        const size_t qs = (size_t)((q0 & 1) ? q0 + 1 : q0) + 1;
+        size_t off = (2 * (tn + 1) * qs + 4 * (tn + 1) + 7 * (size_t)(chunk + 4 * nu + 6)) * sizeof(double);
+        if (!down) off += (size_t)(pd == 1 ? 4 : 8) * C.v.nr * sizeof(double);
+        if (st && down) off += (qs - 1) * 2 * (size_t)(tn + 1) * sizeof(double);
+        stretched |= st;
+        most = std::max(most, std::max(off, (size_t)tn * sizeof(double)));
+    }
+    return most <= (stretched ? 80 : 64) * 1024;
+}
+
+}  // namespace
+
 bool mixed_supported(const cylpoisson_plan* p) {
     if (p->bottom_level < 1 || !bottom_active(p)) return false;
     for (int l = 0; l < p->bottom_level; ++l)
-        if (!fused_supported(p, l)) return false;
+        if (!fused_supported(p, l) || !offered_level(p, l)) return false;
     return true;
 }
 
@@ -594,19 +637,8 @@ cylpoisson_plan* build_plan(cylpoisson_plan* p) {
                 CP_TRY(upload(p, &w8, H.rwp_z));
                 D.tr = Transfer1D{a, w1, w2, b, w3, w4};
                 D.tz = Transfer1D{c, w5, w6, d, w7, w8};
-                // fine column / row -> coincident coarse interior index (or -1)
-                const HostLevel& Hc = p->hl[l + 1];
-                std::vector<int> colc(H.nr, -1), rowc(H.nz, -1);
-                for (int I = 1; I + 1 < Hc.nr; ++I) colc[H.cidx_r[I]] = I;
-                for (int K = 1; K + 1 < Hc.nz; ++K) rowc[H.cidx_z[K]] = K;
-                int *cc, *rc;
-                CP_TRY(upload(p, &cc, colc));
-                CP_TRY(upload(p, &rc, rowc));
-                D.colc = cc;
-                D.rowc = rc;
             }
         }
-        CP_TRY(fused_prepare());
         // the bottom kernel: the first level from 1 on whose levels all fit in LDS
         for (int lb = 1; lb < nl; ++lb) {
             if (bottom_lds_bytes(p, lb) > kBottomLdsBytes) continue;
@@ -940,7 +972,6 @@ int cylpoisson_plan_set_option(cylpoisson_plan* plan, const char* key, double va
     if (!std::strcmp(key, "chunk_rows")) return int_in(0, 1 << 20, &plan->opt.chunk_rows);
     if (!std::strcmp(key, "chunk_rows_coarse")) return int_in(0, 1 << 20, &plan->opt.chunk_rows_coarse);
     if (!std::strcmp(key, "timing")) return int_in(0, 2, &plan->opt.timing);
-    // a fourth row in flight needs more registers than the FP64 up pass has (it spills)
     if (!std::strcmp(key, "prefetch")) return int_in(1, 3, &plan->opt.prefetch);
     if (!std::strcmp(key, "bottom")) return int_in(0, 1, &plan->opt.bottom);
     if (!std::strcmp(key, "smoother")) return int_in(0, 2, &plan->opt.smoother);
