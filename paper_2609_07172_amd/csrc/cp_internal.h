@@ -202,8 +202,10 @@ struct cylpoisson_plan {
 
     // device buffers
     double* d_lam = nullptr;
-    double* d_F = nullptr;       // forward DFT matrix [N][N]
-    double* d_G = nullptr;       // inverse DFT matrix [N][N]
+    double* d_dft = nullptr;     // folded DFT matrices in operand order (dft.hip), N up to 256
+    size_t dft_off[4] = {0, 0, 0, 0};
+    double* d_F = nullptr;       // forward DFT matrix [N][N], larger N
+    double* d_G = nullptr;       // inverse DFT matrix [N][N], larger N
     double* d_s = nullptr;       // s_q = r_i dr_i dz_k / eps0 per level-0 node [nz][nr] (0 on the ring)
     double* d_inv_s = nullptr;   // 1 / s_q (0 on the ring)
     double* d_cinv = nullptr;    // coarsest-level inverse per plane [N][n][n]
@@ -329,6 +331,12 @@ hipError_t launch_refine(const DeviceLevel& L, int nt, const double* lam, const 
 bool fft_supported(int n, long long ncols);
 hipError_t launch_fft(bool inverse, int n, const double* in, double* out, long long ncols,
                       const double* cs, hipStream_t s);
+
+// ---- folded DFT products on the matrix cores (dft.hip) ----
+bool dft_packed(int n);  // Ntheta they serve
+void dft_pack(int n, std::vector<double>& out, size_t (&off)[4]);
+hipError_t launch_dft_packed(bool inverse, const double* A, const size_t (&off)[4], const double* X, double* Y, int n,
+                             long long ncols, const double* colscale, hipStream_t s);
 
 // ---- bottom of the V-cycle (bottom.hip) ----
 size_t bottom_lds_bytes(const cylpoisson_plan* p, int lb);  // FP64 values

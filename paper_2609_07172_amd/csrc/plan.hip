@@ -722,10 +722,16 @@ cylpoisson_plan* build_plan(cylpoisson_plan* p) {
                 d.level = l;
             }
         }
-        std::vector<double> F, G;
-        dft_matrices(Ntheta, F, G);
-        CP_TRY(upload(p, &p->d_F, F));
-        CP_TRY(upload(p, &p->d_G, G));
+        if (dft_packed(Ntheta)) {
+            std::vector<double> A;
+            dft_pack(Ntheta, A, p->dft_off);
+            CP_TRY(upload(p, &p->d_dft, A));
+        } else {
+            std::vector<double> F, G;
+            dft_matrices(Ntheta, F, G);
+            CP_TRY(upload(p, &p->d_F, F));
+            CP_TRY(upload(p, &p->d_G, G));
+        }
         CP_TRY(upload(p, &p->d_lam, p->lam));
         {
             // s_q = r_i dr_i dz_k / eps0 (Eq. mode_rhs) = rb_i zc_k / eps0 on level 0

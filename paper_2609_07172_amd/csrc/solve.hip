@@ -361,13 +361,15 @@ hipError_t join_groups(cylpoisson_plan* p, int G, hipStream_t s) {
 }
 
 // Azimuthal transform of node/plane arrays: register FFT where supported,
-// dense DFT product otherwise.  colscale (forward only) multiplies column
+// folded products on the matrix cores up to 256 azimuths, the dense DFT product
+// beyond.  colscale (forward only) multiplies column
 // c = k Nr + i by colscale[c] (a [Nz][Nr] table).
 hipError_t transform(cylpoisson_plan* p, bool inverse, const double* in, double* out,
                      const double* colscale, hipStream_t s) {
     const long long ncols = (long long)p->nz * p->nr;
     if (p->opt.fft && fft_supported(p->nt, ncols))
         return launch_fft(inverse, p->nt, in, out, ncols, colscale, s);
+    if (p->d_dft) return launch_dft_packed(inverse, p->d_dft, p->dft_off, in, out, p->nt, ncols, colscale, s);
     return launch_dft(inverse ? p->d_G : p->d_F, in, out, p->nt, ncols, colscale, s);
 }
 
