@@ -217,7 +217,8 @@ hipError_t krylov_reserve(cylpoisson_plan* p, int m) {
     // (the V-cycle's residual and the network's correction)
     while ((int)p->kv.size() < 2 * m + 4) {
         double* ptr = nullptr;
-        hipError_t e = hipMalloc(&ptr, bytes);
+        // (the fused passes load a row's last column pair with the value after it)
+        hipError_t e = hipMalloc(&ptr, bytes + 2 * sizeof(double));
         if (e != hipSuccess) return e;
         e = hipMemset(ptr, 0, bytes);  // rings stay zero: Krylov vectors are corrections
         if (e != hipSuccess) return e;
