@@ -428,9 +428,8 @@ cylpoisson_nn* cylpoisson_nn_create(unsigned long long seed) {
         e = hipMalloc(&n.wf[l], 144 * 16 * sizeof(short));
         if (e == hipSuccess) e = hipMalloc(&n.wb[l], 144 * 16 * sizeof(short));
     }
-    if (e == hipSuccess) e = hipMalloc(&n.partial, (size_t)kNetPartials * 9 * 256 * sizeof(float));
-    if (e == hipSuccess) e = hipMalloc(&n.loss_partial, 256 * sizeof(double));
-    if (e == hipSuccess) e = hipHostMalloc((void**)&n.h_loss, 256 * sizeof(double), hipHostMallocDefault);
+    if (e == hipSuccess) e = hipMalloc(&n.partial, net_partial_floats() * sizeof(float));
+    if (e == hipSuccess) e = hipHostMalloc((void**)&n.h_loss, sizeof(double), hipHostMallocDefault);
     if (e == hipSuccess) e = hipMemcpy(n.w, w.data(), total * sizeof(float), hipMemcpyHostToDevice);
     if (e == hipSuccess) e = hipMemset(n.dw, 0, total * sizeof(float));
     if (e == hipSuccess) e = hipMemset(n.m, 0, total * sizeof(float));
@@ -452,7 +451,7 @@ void cylpoisson_nn_destroy(cylpoisson_nn* nn) {
     int prev = 0;
     (void)hipGetDevice(&prev);
     (void)hipSetDevice(n.device);
-    for (float* p : {n.w, n.dw, n.m, n.v, n.partial, n.a1, n.a2, n.y, n.g3, n.g2, n.g1, n.px, n.pt})
+    for (float* p : {n.w, n.dw, n.m, n.v, n.partial, n.a1, n.a2, n.g3, n.px, n.pt})
         if (p) (void)hipFree(p);
     for (int l = 0; l < 3; ++l) {
         if (n.wf[l]) (void)hipFree(n.wf[l]);

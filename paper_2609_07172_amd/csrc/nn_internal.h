@@ -5,7 +5,8 @@
 
 namespace cp {
 
-constexpr int kNetPartials = 512;  // workgroups of a weight-gradient product
+constexpr int kNetPartials = 256;  // workgroups of the backward kernel (one per compute unit)
+constexpr int kNetWgs = 1024;      // workgroups of the forward kernel that run at once
 constexpr int kNetMargin = 3;      // receptive-field radius: the loss skips this border
 constexpr int kPatch = 32;         // training patches are kPatch x kPatch interior nodes
 
@@ -18,12 +19,13 @@ struct NetState {
     float* v = nullptr;
     short* wf[3] = {nullptr, nullptr, nullptr};  // BF16 B operands, forward
     short* wb[3] = {nullptr, nullptr, nullptr};  // BF16 B operands, backward data
-    float* partial = nullptr;   // weight-gradient partials [kNetPartials][9 x 16][16]
-    double* loss_partial = nullptr;
+    float* partial = nullptr;   // weight-gradient partials, one set per backward workgroup
+    double* loss_partial = nullptr;  // per forward workgroup, and their sum at [loss_capacity]
+    long long loss_capacity = 0;
     double* h_loss = nullptr;   // pinned
     // activations and gradients of the last forward/backward, `capacity` pixels
     long long capacity = 0;
-    float *a1 = nullptr, *a2 = nullptr, *y = nullptr, *g3 = nullptr, *g2 = nullptr, *g1 = nullptr;
+    float *a1 = nullptr, *a2 = nullptr, *g3 = nullptr;
     // training set (patches) collected from the solver
     long long patches = 0, patch_capacity = 0;
     float* px = nullptr;  // [patches][kPatch][kPatch][4]
@@ -33,11 +35,8 @@ struct NetState {
 size_t net_weight_offset(int layer);
 int net_total_weights();
 hipError_t net_repack(NetState* n, hipStream_t s);
-hipError_t net_reserve(NetState* n, long long pixels);
-// y = net(x) for B images of H x W (x: 4 channels, y: 2 channels), one kernel
-// per layer with the activations kept in n->a1, n->a2 (for back-propagation)
-hipError_t net_forward(NetState* n, const float* x, float* y, int B, int H, int W, hipStream_t s);
-// The same y from one fused kernel (activations in LDS only): inference
+size_t net_partial_floats();  // size of NetState::partial
+// y = net(x) for B images of H x W (x: 4 channels, y: 2 channels)
 hipError_t net_infer(NetState* n, const float* x, float* y, int B, int H, int W, hipStream_t s);
 // forward, loss on the inner pixels (host value if loss != nullptr) and all weight gradients into dw
 hipError_t net_loss_grad(NetState* n, const float* x, const float* t, int B, int H, int W, double* loss,
