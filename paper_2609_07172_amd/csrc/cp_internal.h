@@ -135,12 +135,11 @@ struct Options {
 };
 
 // Largest interior sizes of a level solved exactly by the separable solve
-// in one workgroup per plane: it holds the plane, its transform, the
-// elimination factors and the axial eigenvectors in LDS (130 KB at 64 x 64).
+// in one workgroup per plane.
 constexpr int kDirectMaxNz = 64;
 constexpr int kDirectMaxNr = 64;
-// Largest interior size each way of the two-kernel form (FP64 matrix-core
-// products; two workgroups per plane, each with half the eigenvectors).
+// Largest interior size each way of the two-kernel form (a workgroup per 32
+// eigenvectors or axial rows of a plane).
 constexpr int kDirectBigMax = 128;
 
 // The cycles from one convergence check to the next, captured into a HIP
@@ -159,11 +158,11 @@ struct GraphSeg {
 struct DirectLevel {
     int level = -1;           // -1: none
     bool big = false;         // a side above 64 interior nodes: the two-kernel form
-    double* V = nullptr;      // one workgroup per plane: V [nzi][nzi]; two-kernel form: [128][128], zero padded
-    double* VT = nullptr;     // two-kernel form: V^T [128][128], zero padded
-    double* M = nullptr;      // two-kernel form: per plane [128][128] elimination factors,
-                              // M[i * 128 + j] = m_i of eigenvector j, zero padded
-    double* sigma = nullptr;  // [nzi] axial eigenvalues
+    // A operands of the two transforms and the elimination factors of every
+    // mode, laid out by direct_pack
+    double* V = nullptr;
+    double* VT = nullptr;
+    double* M = nullptr;
 };
 
 }  // namespace cp
@@ -387,8 +386,10 @@ int checks_end(cylpoisson_plan* p, const CheckCtl& k);
 bool direct_level_ok(const HostLevel& H, int max_nodes);
 // the level's tables: V [nzi][nzi] row-major, eigenvalues [nzi]
 void direct_tables(const HostLevel& H, std::vector<double>& V, std::vector<double>& sigma);
-// the kernels' LDS limits for a level of this size (once, when a plan is built)
-hipError_t direct_prepare(const HostLevel& H, bool big);
+// the packed tables of a level (see direct.hip); lam: shifts of the modes 0 .. nc - 1
+void direct_pack(const HostLevel& H, bool big, const std::vector<double>& V, const std::vector<double>& sigma,
+                 const std::vector<double>& lam, int nc, std::vector<double>& Vp, std::vector<double>& VTp,
+                 std::vector<double>& M);
 // the level the option "direct" selects (-1 when off or none)
 int direct_level(const cylpoisson_plan* p);
 bool direct_active(const cylpoisson_plan* p);

@@ -13,547 +13,327 @@
 // host when the plan is built), A_p u = f becomes, for each axial eigenvector
 // j, one tridiagonal system along r:
 //   (T_r(lambda_p) + sigma_j R_b) w_j = (V^T f)_j,   u = V w.
-// Up to 64 interior nodes each way, each plane is solved exactly (up to
-// rounding) by one workgroup with the whole plane, V and the tables in LDS
-// (k_direct): the axial transform, one elimination per eigenvector (its
-// factors formed as it goes), and the inverse transform written to the
-// level's interior.  Up to 128 each way, two kernels with FP64 matrix-core
-// products and two workgroups per plane do the same (k_direct_fwd,
-// k_direct_inv; see below).  The coarse correction of a V-cycle has a zero
-// Dirichlet ring, so only interior values enter and only interior values are
-// written.
+// The transforms are dense contractions and run on the FP64 matrix cores
+// (v_mfma_f64_16x16x4f64: D += A B with A 16 x 4, B 4 x 16; lane l holds
+// A[l % 16][l / 16], B[l / 16][l % 16] and D[l / 16 + 4q][l % 16], q < 4), V and
+// V^T packed in the A operand's lane order when the plan is built.  The
+// eliminations use factors formed then too (per mode: their chain is a
+// division a row), which leaves one fused multiply-add a row,
+//   d_i = (rw_i m_i) d_{i-1} + m_i g_i,   w_i = (re_i m_i) w_{i+1} + d_i,
+// and run as segmented recurrences: a lane takes four rows of one eigenvector,
+// the segments of an eigenvector are neighbouring lanes, and the carry into
+// each segment is a scan of their affine maps by cross-lane moves; the
+// rows are then run again from the carry.  Rows past the last have m = 0, which
+// makes them zero.
+//
+// Up to 64 interior nodes each way, one workgroup solves a plane with
+// everything between the two transforms in LDS (k_direct).  Up to 128, a plane
+// is more matrix work than one compute unit should do alone: k_direct_fwd
+// takes 32 eigenvectors of a plane per workgroup and writes w to the level's r
+// array (free where the V-cycle stops), k_direct_inv 32 axial rows.  The
+// workgroups of a plane run on one XCD, whose L2 serves all but the first read
+// of f and w.  The coarse correction of a V-cycle has a zero Dirichlet ring, so
+// only interior values enter and only interior values are written.
+//
+// What bounds it: latency (a workgroup's loads, products, scan and stores
+// follow one another) and, at 128 planes of 99 x 127, 7 us of the matrix cores
+// a transform.  One workgroup per plane: 3.9 us at 16 planes of 15 x 15 (8.3
+// with the products on the vector unit and one lane per eigenvector dividing
+// its way along r), 13 us at 64 planes of 63 x 63 (33).  Two kernels: 10 + 9 us
+// at 45 planes of 74 x 100 (18 + 12 in halves of a plane with one chain of a
+// ninth of the rows per lane), 9 + 7 at 64 of 49 x 99 (14 + 9), 23 + 20 at 128 of
+// 99 x 127 (26 + 18).
 
 #include "cp_internal.h"
 
 #include <algorithm>
 #include <cmath>
-#include <map>
 
 namespace cp {
 
 namespace {
 
-constexpr int kDirThreads = 1024;
+typedef double dbl4 __attribute__((ext_vector_type(4)));
+
+constexpr int kSegRows = 4;  // rows of an elimination segment (one lane)
 
 struct DirectArgs {
     LevelView v;          // the direct level
     const double* f;      // right-hand side (the level's f)
     double* u;            // answer (the level's u; its ring stays zero)
-    const double* V;      // [nzi][nzi], V[k * nzi + j]
-    const double* sigma;  // [nzi] axial eigenvalues
-    const double* lam;    // per plane
+    double* w;            // two-kernel form: w [nzi][nri] of each plane between the kernels
+    const double* V;      // A operands of V^T, [group][k-step][lane]
+    const double* VT;     // A operands of V
+    const double* M;      // elimination factors, [mode][group][row of segment][chain and segment]
     const int* mask;      // per plane: 0 = frozen, or nullptr
-    int p0;
+    int p0, np;           // planes p0 .. p0 + np - 1
+    int nc;               // cosine planes (the sine planes after them repeat modes 1, 2, ...)
+    int ks;               // k-steps of the packed operands
 };
 
-// LDS layout (doubles): V [nzp][nzp], f [nzi][nrp], g [nzi][nrp] (the
-// transformed values, then the eliminated and solved ones), c [nzi][nrp] (the
-// elimination's c_i), sigma [nzp], radial tables rw, re, rb, rm [nrp] each;
-// nzp = nzi rounded up to 2, nrp = nri rounded up to 4 (whole register tiles).
-__host__ __device__ inline int dir_nzp(int nzi) { return (nzi + 1) & ~1; }
-__host__ __device__ inline int dir_nrp(int nri) { return (nri + 3) & ~3; }
-__host__ __device__ inline size_t dir_lds_doubles(int nzi, int nri) {
-    const size_t nzp = dir_nzp(nzi), nrp = dir_nrp(nri);
-    return nzp * nzp + 3 * (size_t)nzi * nrp + nzp + 4 * nrp;
-}
+__device__ __forceinline__ int mode_of(int plane, int nc) { return plane < nc ? plane : plane - nc + 1; }
 
-// out[r][i] = sum_x A(x, r) S[x][i] over one plane in LDS, in 2 x 4 register
-// tiles (thread t < ceil(nzi / 2) ceil(nri / 4)); A(x, r) = V[x][r] (TRANS:
-// the axial transform V^T S) or V[r][x] (the inverse transform V S).  The
-// tiles' padding rows and columns are computed and not stored.
-template <bool TRANS>
-__device__ __forceinline__ void dir_product(const double* Vs, int nzp, const double* S, int nrp, int nzi, int nri,
-                                            int t, double (&acc)[2][4], int* r0, int* i0) {
-    const int nti = nrp / 4;
-    *r0 = 2 * (t / nti);
-    *i0 = 4 * (t % nti);
+// The elimination factors and radial couplings of a lane's four rows.
+struct SegTables {
+    double m[kSegRows], rw[kSegRows], re[kSegRows];
+    __device__ __forceinline__ void load(const LevelView& v, const double* M, int stride, int seg) {
+        const int nri = v.nr - 2;
 #pragma unroll
-    for (int a = 0; a < 2; ++a)
+        for (int u = 0; u < kSegRows; ++u) {
+            const int i = seg * kSegRows + u;
+            m[u] = M[(size_t)u * stride];
+            rw[u] = i < nri ? v.rw[i + 1] : 0.0;
+            re[u] = i < nri ? v.re[i + 1] : 0.0;
+        }
+    }
+};
+
+// Both recurrences of a lane's segment: g in, w out.  NSEG lanes of a
+// wavefront hold the segments of one eigenvector, in order.
+template <int NSEG>
+__device__ __forceinline__ void eliminate(const SegTables& tb, double (&g)[kSegRows], int seg) {
+    double q[kSegRows];
+    {
+        double d = 0.0, P = 1.0;
 #pragma unroll
-        for (int b = 0; b < 4; ++b) acc[a][b] = 0.0;
-    for (int x = 0; x < nzi; ++x) {
-        const double a0 = TRANS ? Vs[x * nzp + *r0] : Vs[*r0 * nzp + x];
-        const double a1 = TRANS ? Vs[x * nzp + *r0 + 1] : Vs[(*r0 + 1) * nzp + x];
-        const double2 s01 = *reinterpret_cast<const double2*>(S + x * nrp + *i0);
-        const double2 s23 = *reinterpret_cast<const double2*>(S + x * nrp + *i0 + 2);
-        const double sv[4] = {s01.x, s01.y, s23.x, s23.y};
+        for (int u = 0; u < kSegRows; ++u) {
+            q[u] = tb.rw[u] * tb.m[u];
+            g[u] *= tb.m[u];
+            d = fma(q[u], d, g[u]);
+            P *= q[u];
+        }
 #pragma unroll
-        for (int b = 0; b < 4; ++b) {
-            acc[0][b] = fma(a0, sv[b], acc[0][b]);
-            acc[1][b] = fma(a1, sv[b], acc[1][b]);
+        for (int o = 1; o < NSEG; o <<= 1) {
+            const double Pp = __shfl_up(P, o, NSEG), dp = __shfl_up(d, o, NSEG);
+            if (seg >= o) {
+                d = fma(P, dp, d);
+                P *= Pp;
+            }
+        }
+        double c = __shfl_up(d, 1, NSEG);
+        if (seg == 0) c = 0.0;
+#pragma unroll
+        for (int u = 0; u < kSegRows; ++u) {
+            c = fma(q[u], c, g[u]);
+            g[u] = c;
+        }
+    }
+    {
+        double w = 0.0, P = 1.0;
+#pragma unroll
+        for (int u = kSegRows - 1; u >= 0; --u) {
+            q[u] = tb.re[u] * tb.m[u];
+            w = fma(q[u], w, g[u]);
+            P *= q[u];
+        }
+#pragma unroll
+        for (int o = 1; o < NSEG; o <<= 1) {
+            const double Pp = __shfl_down(P, o, NSEG), wp = __shfl_down(w, o, NSEG);
+            if (seg + o < NSEG) {
+                w = fma(P, wp, w);
+                P *= Pp;
+            }
+        }
+        double c = __shfl_down(w, 1, NSEG);
+        if (seg == NSEG - 1) c = 0.0;
+#pragma unroll
+        for (int u = kSegRows - 1; u >= 0; --u) {
+            c = fma(q[u], c, g[u]);
+            g[u] = c;
         }
     }
 }
 
-// One workgroup per plane: the exact solve of the direct level's system
-// A_p u = f (see the top of the file) with every value in LDS.
-__global__ __launch_bounds__(kDirThreads) void k_direct(DirectArgs a) {
-    extern __shared__ double smem[];
+// One workgroup per plane, up to 16 G interior nodes each way: G x G wavefronts,
+// wavefront (g, c) forms the 16 x 16 tile of group g and radial columns 16 c of
+// each transform, and a lane one segment of one eigenvector between them.
+template <int G>
+__global__ void __launch_bounds__(64 * G * G) k_direct(DirectArgs a) {
+    constexpr int N = 16 * G, NSEG = 4 * G, KS = 4 * G, LD = N + 1;
+    __shared__ double gs[N * LD];
+    const LevelView& v = a.v;
     const int plane = a.p0 + blockIdx.x;
     if (a.mask && a.mask[plane] == 0) return;  // whole workgroup, before any barrier
-    const LevelView& v = a.v;
     const int nzi = v.nz - 2, nri = v.nr - 2;
-    const int nzp = dir_nzp(nzi), nrp = dir_nrp(nri);
-    double* Vs = smem;
-    double* Fs = Vs + nzp * nzp;
-    double* Gs = Fs + nzi * nrp;
-    double* Cs = Gs + nzi * nrp;
-    double* sig = Cs + nzi * nrp;
-    double* rw = sig + nzp;
-    double* re = rw + nrp;
-    double* rb = re + nrp;
-    double* rm = rb + nrp;
-    const int t = threadIdx.x;
-    const double* f = a.f + (size_t)plane * v.pstride + v.pitch + 1;  // interior (0, 0)
+    const int t = threadIdx.x, wave = t >> 6, l = t & 63, kr = l >> 4, cl = l & 15;
+    const int grp = wave / G, col = 16 * (wave % G) + cl;
+    const size_t base = (size_t)plane * v.pstride + v.pitch + 1;  // interior (0, 0)
+    const bool in = col < nri;
+    double fb[KS], va[KS];
+#pragma unroll
+    for (int s = 0; s < KS; ++s) {
+        const int k = 4 * s + kr;
+        fb[s] = in && k < nzi ? a.f[base + (size_t)k * v.pitch + col] : 0.0;
+        va[s] = a.V[((size_t)grp * KS + s) * 64 + l];
+    }
+    const int chain = t / NSEG, seg = t % NSEG;
+    SegTables tb;
+    tb.load(v, a.M + ((size_t)mode_of(plane, a.nc) * G + chain / 16) * (kSegRows * 16 * NSEG) + t % (16 * NSEG),
+            16 * NSEG, seg);
+    dbl4 acc = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+    for (int s = 0; s < KS; ++s) acc = __builtin_amdgcn_mfma_f64_16x16x4f64(va[s], fb[s], acc, 0, 0, 0);
+#pragma unroll
+    for (int q = 0; q < 4; ++q) gs[(16 * grp + kr + 4 * q) * LD + col] = acc[q];
+    __syncthreads();
     {
-        // every load in flight before the stores: element q = t + 1024 u of
-        // f's interior (row q / nri) and of V (row q / nzi); zero padding
-        constexpr int U = kDirectMaxNz * kDirectMaxNr / kDirThreads;
-        static_assert(kDirectMaxNz * kDirectMaxNz <= U * kDirThreads, "V fits the staging");
-        double sf[U], sv[U];
+        double g[kSegRows];
+        double* row = gs + chain * LD + seg * kSegRows;
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const int q = t + u * kDirThreads;
-            const int k = q / nri, i = q - k * nri;
-            sf[u] = q < nzi * nri ? f[(size_t)k * v.pitch + i] : 0.0;
-            sv[u] = q < nzi * nzi ? a.V[q] : 0.0;
-        }
-        for (int q = t; q < nzp * nzp; q += kDirThreads) Vs[q] = 0.0;
-        for (int q = t; q < nzi * nrp; q += kDirThreads) Fs[q] = 0.0;
-        if (t < nzp) sig[t] = t < nzi ? a.sigma[t] : 0.0;
-        if (t < nrp) {
-            const bool in = t < nri;
-            rw[t] = in ? v.rw[t + 1] : 0.0;
-            re[t] = in ? v.re[t + 1] : 0.0;
-            rb[t] = in ? v.rb[t + 1] : 0.0;
-            rm[t] = in ? v.rm[t + 1] : 0.0;
-        }
-        __syncthreads();
+        for (int u = 0; u < kSegRows; ++u) g[u] = row[u];
+        eliminate<NSEG>(tb, g, seg);
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const int q = t + u * kDirThreads;
-            if (q < nzi * nri) {
-                const int k = q / nri, i = q - k * nri;
-                Fs[k * nrp + i] = sf[u];
-            }
-            if (q < nzi * nzi) {
-                const int k = q / nzi, j = q - k * nzi;
-                Vs[k * nzp + j] = sv[u];
-            }
-        }
+        for (int u = 0; u < kSegRows; ++u) row[u] = g[u];
     }
+#pragma unroll
+    for (int s = 0; s < KS; ++s) va[s] = a.VT[((size_t)grp * KS + s) * 64 + l];
     __syncthreads();
-    const int tiles = (nzp / 2) * (nrp / 4);
-    // g = V^T f
-    if (t < tiles) {
-        double acc[2][4];
-        int r0, i0;
-        dir_product<true>(Vs, nzp, Fs, nrp, nzi, nri, t, acc, &r0, &i0);
+    acc = dbl4{0.0, 0.0, 0.0, 0.0};
 #pragma unroll
-        for (int r = 0; r < 2; ++r)
+    for (int s = 0; s < KS; ++s)
+        acc = __builtin_amdgcn_mfma_f64_16x16x4f64(va[s], gs[(4 * s + kr) * LD + col], acc, 0, 0, 0);
+    if (!in) return;
 #pragma unroll
-            for (int b = 0; b < 4; ++b)
-                if (r0 + r < nzi) Gs[(r0 + r) * nrp + i0 + b] = acc[r][b];
-    }
-    __syncthreads();
-    // one radial tridiagonal system per eigenvector j:
-    //   b_i = rw_i + re_i + lambda rm_i + sigma_j rb_i,  m_i = 1 / (b_i - rw_i c_{i-1}),
-    //   c_i = re_i m_i,  d_i = (g_i + rw_i d_{i-1}) m_i,  w_i = d_i + c_i w_{i+1}
-    if (t < nzi) {
-        const double lam = a.lam[plane], sj = sig[t];
-        double* g = Gs + t * nrp;
-        double* c = Cs + t * nrp;
-        double cp = 0.0, d = 0.0;
-        for (int i = 0; i < nri; ++i) {
-            const double b = fma(sj, rb[i], fma(lam, rm[i], rw[i] + re[i]));
-            const double m = 1.0 / (b - rw[i] * cp);
-            d = (g[i] + rw[i] * d) * m;
-            cp = re[i] * m;
-            g[i] = d;
-            c[i] = cp;
-        }
-        double w = 0.0;
-        for (int i = nri - 1; i >= 0; --i) {
-            w = fma(c[i], w, g[i]);
-            g[i] = w;
-        }
-    }
-    __syncthreads();
-    // u = V w, into the level's interior
-    if (t < tiles) {
-        double acc[2][4];
-        int r0, i0;
-        dir_product<false>(Vs, nzp, Gs, nrp, nzi, nri, t, acc, &r0, &i0);
-        double* u = a.u + (size_t)plane * v.pstride + v.pitch + 1;
-#pragma unroll
-        for (int r = 0; r < 2; ++r)
-#pragma unroll
-            for (int b = 0; b < 4; ++b)
-                if (r0 + r < nzi && i0 + b < nri) u[(size_t)(r0 + r) * v.pitch + i0 + b] = acc[r][b];
+    for (int q = 0; q < 4; ++q) {
+        const int k = 16 * grp + kr + 4 * q;
+        if (k < nzi) a.u[base + (size_t)k * v.pitch + col] = acc[q];
     }
 }
 
 // ---- two-kernel form: up to 128 interior nodes each way ----
-//
-// Both transforms are dense contractions over 128-point axes, done on the
-// FP64 matrix cores (v_mfma_f64_16x16x4f64: D += A B with A 16 x 4, B 4 x 16;
-// lane l holds A[l % 16][l / 16], B[l / 16][l % 16] and D[l / 16 + 4q][l % 16],
-// q < 4; checked on the device).  Workgroup (h, plane) owns eigenvectors 64h .. 64h + 63 in the first
-// kernel and axial rows 64h .. 64h + 63 in the second, so 128 planes fill 256
-// compute units; wave w owns radial columns 16w .. 16w + 15, whose values it
-// keeps in registers for every k-step, while the eigenvector half sits in LDS.
-//   k_direct_fwd: g = V^T f for its eigenvectors, then the waves
-//     eliminate and back-substitute each eigenvector's system with the
-//     elimination factors m_i formed when the plan is built (per plane and
-//     eigenvector: the factor chain is a division per step, and on the FP64
-//     pipe the matrix products share it would run after them, not beside
-//     them), and the workgroup writes w [nzi][nri] to the level's r array
-//     (free at the level where the V-cycle stops).
-//   k_direct_inv: u = V w for its rows, into the level's interior.
-// Padded rows and columns of V (beyond nzi) are zero, and so are the
-// operands loaded beyond the level, so the padding adds nothing.
 
-typedef double dbl4 __attribute__((ext_vector_type(4)));
+constexpr int kBigThreads = 512, kBigSegs = 32;  // eight column tiles; 16 chains of 32 segments
+// Groups of 16 per workgroup.  One alone (operands in registers) reads f and w
+// twice as often: 37 + 27 us at 128 planes of 99 x 127 against 23 + 20, 14 + 10
+// against 10 + 9 at 45 planes of 74 x 100; four (one workgroup per compute unit,
+// no other to overlap its phases) 24 + 23 and 15 + 13.
+constexpr int kBigE = 2;
 
-constexpr int kBigHalf = 64;                                  // eigenvectors / rows per workgroup
-constexpr int kBigSteps = kDirectBigMax / 4;                  // k-steps of one product
-constexpr int kBigWaves = kDirectBigMax / 16;                 // product waves (16 radial columns each)
-constexpr int kBigFwdThreads = (kBigWaves + 1) * 64;          // + the elimination wave
-constexpr int kBigInvThreads = kBigWaves * 64;
-constexpr int kBigLdg = kDirectBigMax + 1;                    // LDS pitch of g's rows (odd)
-constexpr int kBigV = kDirectBigMax * kBigHalf;               // one half of V (or V^T) in LDS
-constexpr int kBigVG = kBigV > kBigHalf * kBigLdg ? kBigV : kBigHalf * kBigLdg;
-constexpr int kBigFwdLds = kBigVG + kDirectBigMax * kBigHalf + 2 * kDirectBigMax + 3 * (kBigWaves + 1) * kBigHalf;
-constexpr int kBigInvLds = kBigV;
-constexpr int kBigSeg = 16;                                   // rows per wave's elimination segment (>= 128 / 9)
-static_assert(kBigSeg * (kBigWaves + 1) >= kDirectBigMax, "the segments cover every row");
-
-struct BigArgs {
-    LevelView v;
-    const double* f;      // right-hand side (the level's f)
-    double* u;            // answer (the level's u; its ring stays zero)
-    double* w;            // the level's r array: per plane w [nzi][nri] between the kernels
-    const double* V;      // [128][128], V[k * 128 + j], zero padded
-    const double* VT;     // [128][128], VT[j * 128 + k], zero padded
-    const double* M;      // per plane [128][128]: M[i * 128 + j] = m_i of eigenvector j, zero padded
-    const int* mask;      // per plane: 0 = frozen, or nullptr
-    int p0, np;           // planes p0 .. p0 + np - 1
-};
-
-// Halves of padded 128 x 128 tables, dst[q] = src[(q / 64) * 128 + col0 + q % 64]
-// for q < lim (lim <= 128 * 64: whole rows of the half), in two steps so that
-// other loads can be issued between them: the loads into registers, then the
-// stores to LDS.  Indices past lim are clamped to its last element, which
-// those threads then store again with its own value, so no store needs a branch.
-template <int T, int NT>
-struct HalfStage {
-    static constexpr int N = (kBigV + T - 1) / T;
-    double x[NT][N];
-    __device__ __forceinline__ void load(const double* const (&src)[NT], const int (&lim)[NT], int col0, int t) {
-#pragma unroll
-        for (int u = 0; u < N; ++u)
-#pragma unroll
-            for (int b = 0; b < NT; ++b) {
-                const int q = min(u * T + t, lim[b] - 1);
-                x[b][u] = src[b][(q >> 6) * kDirectBigMax + col0 + (q & 63)];
-            }
-    }
-    __device__ __forceinline__ void store(double* const (&dst)[NT], const int (&lim)[NT], int t) const {
-#pragma unroll
-        for (int u = 0; u < N; ++u)
-#pragma unroll
-            for (int b = 0; b < NT; ++b) dst[b][min(u * T + t, lim[b] - 1)] = x[b][u];
-    }
-};
-
-// Workgroup -> (half, plane) of the two-kernel form.  With two halves, the
-// halves of one plane are 8 workgroups apart: workgroups are dealt to the 8
-// XCDs in turn, so both run on one XCD and the second finds the plane's input
-// in that XCD's L2.  False for the padding workgroups of the last group.
-__device__ __forceinline__ bool big_block(int halves, int np, int* h, int* p) {
-    const int id = blockIdx.x;
-    if (halves == 1) {
-        *h = 0;
-        *p = id;
-    } else {
-        *h = (id >> 3) & 1;
-        *p = (id >> 4) * 8 + (id & 7);
-    }
-    return *p < np;
+// Workgroup -> (plane, first group); the workgroups of one plane are dealt to
+// one of the eight XCDs.  False for the padding workgroups of the last eight
+// planes.
+__device__ __forceinline__ bool big_block(int groups, int np, int* plane, int* g) {
+    const int idx = (int)blockIdx.x >> 3, per = (groups + kBigE - 1) / kBigE;
+    *plane = (idx / per) * 8 + ((int)blockIdx.x & 7);
+    *g = (idx % per) * kBigE;
+    return *plane < np;
 }
-__host__ inline int big_blocks(int halves, int np) { return halves == 1 ? np : 16 * ((np + 7) / 8); }
 
-// Transform and eliminations.  Waves 0 .. ceil(nri / 16) - 1 form g = V^T f
-// for their radial columns; then all nine waves run the eliminations,
-//   d_i = m_i g_i + (rw_i m_i) d_{i-1},  w_i = d_i + (re_i m_i) w_{i+1}
-// (one fused multiply-add per step on each chain), each on one segment of
-// the rows (see below).
-__global__ __launch_bounds__(kBigFwdThreads) void k_direct_fwd(BigArgs a) {
-    extern __shared__ double smem[];
-    const LevelView v = a.v;
+// The products of a workgroup's groups: B operands src[k * pitch + col], k < n,
+// in registers and the A operands in LDS (`as`, kBigE ks 64 values), where
+// every wavefront reads them, all loaded at once.  Every thread of the
+// workgroup calls it; wavefronts past the last column tile (!on) only stage.
+template <int KS>
+__device__ __forceinline__ void product(const double* __restrict__ A, int ks, int groups, int g0, double* as,
+                                        const double* __restrict__ src, size_t pitch, int n, int col, bool on, bool in,
+                                        int l, dbl4 (&acc)[kBigE]) {
+    constexpr int NA = (kBigE * KS * 32 + kBigThreads - 1) / kBigThreads;  // 16-byte pieces per thread
+    const double2* ag = reinterpret_cast<const double2*>(A + (size_t)g0 * ks * 64);
+    double fb[KS];
+    double2 st[NA];
+    // pieces past the last group's repeat its last one
+    const int pieces = min(kBigE, groups - g0) * ks * 32;
+#pragma unroll
+    for (int i = 0; i < NA; ++i) st[i] = ag[min((int)threadIdx.x + i * kBigThreads, pieces - 1)];
+#pragma unroll
+    for (int s = 0; s < KS; ++s) {
+        const int k = 4 * s + (l >> 4);
+        fb[s] = in && k < n ? src[(size_t)k * pitch + col] : 0.0;
+    }
+#pragma unroll
+    for (int i = 0; i < NA; ++i)
+        reinterpret_cast<double2*>(as)[min((int)threadIdx.x + i * kBigThreads, pieces - 1)] = st[i];
+    __syncthreads();
+#pragma unroll
+    for (int e = 0; e < kBigE; ++e) acc[e] = dbl4{0.0, 0.0, 0.0, 0.0};
+    if (!on) return;
+    // (a group past the last multiplies the staging of the one before it or
+    // what the LDS held: its results are not used)
+#pragma unroll
+    for (int s = 0; s < KS; ++s)
+        if (s < ks)
+#pragma unroll
+            for (int e = 0; e < kBigE; ++e)
+                acc[e] = __builtin_amdgcn_mfma_f64_16x16x4f64(as[((size_t)min(e, groups - 1 - g0) * ks + s) * 64 + l],
+                                                              fb[s], acc[e], 0, 0, 0);
+}
+
+// Transform and eliminations of 32 eigenvectors.
+template <int KS>
+__global__ void __launch_bounds__(kBigThreads, 4) k_direct_fwd(DirectArgs a) {
+    constexpr int LD = kDirectBigMax + 1;
+    __shared__ double gs[16 * kBigE * LD];
+    __shared__ __attribute__((aligned(16))) double as[kBigE * KS * 64];
+    const LevelView& v = a.v;
     const int nzi = v.nz - 2, nri = v.nr - 2;
-    int h, pl;
-    if (!big_block((nzi + kBigHalf - 1) / kBigHalf, a.np, &h, &pl)) return;  // whole workgroup
+    const int groups = (nzi + 15) / 16;
+    int pl, g0;
+    if (!big_block(groups, a.np, &pl, &g0)) return;  // whole workgroup
     const int plane = a.p0 + pl;
     if (a.mask && a.mask[plane] == 0) return;  // whole workgroup, before any barrier
-    const int nrt = (nri + 15) / 16;
     const int t = threadIdx.x, wave = t >> 6, l = t & 63;
-    const int j0 = h * kBigHalf, nj = min(kBigHalf, nzi - j0);
-    const int ks = (nzi + 3) / 4;
-    double* VG = smem;  // V's half [k][64], later g [64][kBigLdg]
-    double* M = VG + kBigVG;  // factors [i][64]
-    double* rw = M + kDirectBigMax * kBigHalf;
-    double* re = rw + kDirectBigMax;
-    // V's half whole (the products read rows up to 4 ceil(nzi / 4) - 1); the
-    // factors' rows the eliminations' blocks reach (rows past nri are zero)
-    HalfStage<kBigFwdThreads, 2> stage;
-    const int lim[2] = {kBigV, nri * kBigHalf};
+    const int col = 16 * wave + (l & 15);
+    const int chain = t / kBigSegs, seg = t % kBigSegs;
     {
-        const double* const src[2] = {a.V, a.M + (size_t)plane * kDirectBigMax * kDirectBigMax};
-        stage.load(src, lim, j0, t);
-    }
-    // this wave's columns of f (the products' B operands); values outside the
-    // level are zero (exec-masked loads into zeroed registers)
-    double fb[kBigSteps];
-    {
-        const double* f = a.f + (size_t)plane * v.pstride + v.pitch + 1;  // interior (0, 0)
-        const int r = 16 * wave + (l & 15);
-        const bool col = wave < nrt && r < nri;
+        dbl4 acc[kBigE];
+        product<KS>(a.V, a.ks, groups, g0, as, a.f + (size_t)plane * v.pstride + v.pitch + 1, v.pitch, nzi, col,
+                    16 * wave < nri, col < nri, l, acc);
+        if (16 * wave < nri)
 #pragma unroll
-        for (int s = 0; s < kBigSteps; ++s) {
-            const int k = 4 * s + (l >> 4);
-            fb[s] = col && k < nzi ? f[k * v.pitch + r] : 0.0;
-        }
+            for (int e = 0; e < kBigE; ++e)
+#pragma unroll
+                for (int q = 0; q < 4; ++q) gs[(16 * e + (l >> 4) + 4 * q) * LD + col] = acc[e][q];
     }
-    if (t < kDirectBigMax) {
-        const bool in = t < nri;
-        rw[t] = in ? v.rw[t + 1] : 0.0;
-        re[t] = in ? v.re[t + 1] : 0.0;
-    }
-    {
-        double* const dst[2] = {VG, M};
-        stage.store(dst, lim, t);
-    }
+    SegTables tb[kBigE];
+#pragma unroll
+    for (int e = 0; e < kBigE; ++e)
+        tb[e].load(v, a.M + ((size_t)mode_of(plane, a.nc) * groups + min(g0 + e, groups - 1)) * (kSegRows * kBigThreads) + t,
+                   kBigThreads, seg);
     __syncthreads();
-    dbl4 acc[4];
-    if (wave < nrt) {
-        // g[j][r] = sum_k V[k][j0 + j] f[k][r] for this wave's 16 columns, 4 tiles of 16 eigenvectors
 #pragma unroll
-        for (int jt = 0; jt < 4; ++jt) acc[jt] = dbl4{0.0, 0.0, 0.0, 0.0};
-        // the next step's V operands are read from LDS before this step's products issue
-        const double* vcol = VG + (l >> 4) * kBigHalf + (l & 15);
-        double an[4];
+    for (int e = 0; e < kBigE; ++e) {
+        const int j = 16 * (g0 + e) + chain;
+        double g[kSegRows];
 #pragma unroll
-        for (int jt = 0; jt < 4; ++jt) an[jt] = vcol[16 * jt];
-#pragma unroll
-        for (int s = 0; s < kBigSteps; ++s) {
-            if (s < ks) {
-                double ac[4];
-#pragma unroll
-                for (int jt = 0; jt < 4; ++jt) ac[jt] = an[jt];
-                if (s + 1 < kBigSteps) {
-                    const double* vrow = vcol + 4 * (s + 1) * kBigHalf;
-#pragma unroll
-                    for (int jt = 0; jt < 4; ++jt) an[jt] = vrow[16 * jt];
-                }
-#pragma unroll
-                for (int jt = 0; jt < 4; ++jt)
-                    acc[jt] = __builtin_amdgcn_mfma_f64_16x16x4f64(ac[jt], fb[s], acc[jt], 0, 0, 0);
-            }
+        for (int u = 0; u < kSegRows; ++u) {
+            const int i = seg * kSegRows + u;
+            g[u] = i < nri ? gs[(16 * e + chain) * LD + i] : 0.0;
         }
-    }
-    __syncthreads();  // every wave's reads of V are done before g overwrites it
-    if (wave < nrt) {
+        eliminate<kBigSegs>(tb[e], g, seg);
+        if (j < nzi) {
+            double* wout = a.w + (size_t)plane * v.pstride + (size_t)j * nri + seg * kSegRows;
 #pragma unroll
-        for (int jt = 0; jt < 4; ++jt)
-#pragma unroll
-            for (int q = 0; q < 4; ++q)
-                VG[(16 * jt + (l >> 4) + 4 * q) * kBigLdg + 16 * wave + (l & 15)] = acc[jt][q];
-    }
-    __syncthreads();
-    // The eliminations as segmented recurrences: wave w takes rows
-    // [w L, (w + 1) L) of every eigenvector (lane j), so each chain is L steps
-    // long instead of nri.  Forward, d_i = q_i d_{i-1} + e_i with q_i = rw_i m_i,
-    // e_i = m_i g_i: each segment runs from zero and keeps the product of its
-    // q_i; one wave then carries the true d into every segment; each segment
-    // adds carry times its running product.  Back substitution, w_i = c_i
-    // w_{i+1} + d_i with c_i = re_i m_i, the same from the top.  Steps past a
-    // segment's end are identities (factor 1, term 0), so no branch sits on a
-    // chain.
-    {
-        constexpr int S = kBigWaves + 1;
-        const int L = (nri + S - 1) / S;
-        const int i0 = wave * L, len = max(0, min(L, nri - i0));
-        double* g = VG + l * kBigLdg;
-        double* Pe = M + kDirectBigMax * kBigHalf + 2 * kDirectBigMax;  // [S][64] segment products
-        double* De = Pe + S * kBigHalf;                                   // [S][64] segment ends
-        double* Ci = De + S * kBigHalf;                                   // [S][64] carries in
-        const bool lane_on = l < nj;
-        double fac[kBigSeg], val[kBigSeg];
-        // forward: local recurrences
-        {
-#pragma unroll
-            for (int u = 0; u < kBigSeg; ++u) {
-                const int i = min(i0 + u, kDirectBigMax - 1);
-                const double m = M[i * kBigHalf + l];
-                const bool in = u < len;
-                fac[u] = in ? rw[i] * m : 1.0;
-                val[u] = in ? g[i] * m : 0.0;
-            }
-            double d = 0.0, P = 1.0;
-#pragma unroll
-            for (int u = 0; u < kBigSeg; ++u) {
-                d = fma(fac[u], d, val[u]);
-                P *= fac[u];
-                val[u] = d;
-            }
-#pragma unroll
-            for (int u = 0; u < kBigSeg; ++u)
-                if (u < len && lane_on) g[i0 + u] = val[u];
-            Pe[wave * kBigHalf + l] = P;
-            De[wave * kBigHalf + l] = d;
+            for (int u = 0; u < kSegRows; ++u)
+                if (seg * kSegRows + u < nri) wout[u] = g[u];
         }
-        __syncthreads();
-        if (wave == 0) {
-            double d = 0.0;
-            for (int w = 0; w < S; ++w) {
-                Ci[w * kBigHalf + l] = d;
-                d = fma(Pe[w * kBigHalf + l], d, De[w * kBigHalf + l]);
-            }
-        }
-        __syncthreads();
-        {
-            const double c = Ci[wave * kBigHalf + l];
-            double P = 1.0;
-#pragma unroll
-            for (int u = 0; u < kBigSeg; ++u) {
-                P *= fac[u];
-                if (u < len && lane_on) g[i0 + u] = fma(P, c, g[i0 + u]);
-            }
-        }
-        __syncthreads();
-        // back substitution: local recurrences from the segment's top row down
-        {
-#pragma unroll
-            for (int u = 0; u < kBigSeg; ++u) {
-                const int i = min(max(i0 + len - 1 - u, 0), kDirectBigMax - 1);
-                const bool in = u < len;
-                const double m = M[i * kBigHalf + l];
-                fac[u] = in ? re[i] * m : 1.0;
-                val[u] = in ? g[i] : 0.0;
-            }
-            double w = 0.0, P = 1.0;
-#pragma unroll
-            for (int u = 0; u < kBigSeg; ++u) {
-                w = fma(fac[u], w, val[u]);
-                P *= fac[u];
-                val[u] = w;
-            }
-#pragma unroll
-            for (int u = 0; u < kBigSeg; ++u)
-                if (u < len && lane_on) g[i0 + len - 1 - u] = val[u];
-            Pe[wave * kBigHalf + l] = P;
-            De[wave * kBigHalf + l] = w;
-        }
-        __syncthreads();
-        if (wave == 0) {
-            double w = 0.0;
-            for (int sg = S - 1; sg >= 0; --sg) {
-                Ci[sg * kBigHalf + l] = w;
-                w = fma(Pe[sg * kBigHalf + l], w, De[sg * kBigHalf + l]);
-            }
-        }
-        __syncthreads();
-        {
-            const double c = Ci[wave * kBigHalf + l];
-            double P = 1.0;
-#pragma unroll
-            for (int u = 0; u < kBigSeg; ++u) {
-                P *= fac[u];
-                const int i = i0 + len - 1 - u;
-                if (u < len && lane_on) g[i] = fma(P, c, g[i]);
-            }
-        }
-    }
-    __syncthreads();
-    double* wout = a.w + (size_t)plane * v.pstride + (size_t)j0 * nri;
-    for (int q = t; q < nj * nri; q += kBigFwdThreads) {
-        const int j = q / nri, i = q - j * nri;
-        wout[q] = VG[j * kBigLdg + i];
     }
 }
 
-// Inverse transform: waves 0 .. ceil(nri / 16) - 1 form u = V w for their
-// radial columns and this workgroup's 64 axial rows.
-__global__ __launch_bounds__(kBigInvThreads) void k_direct_inv(BigArgs a) {
-    extern __shared__ double smem[];
-    const LevelView v = a.v;
+// Inverse transform of 32 axial rows.
+template <int KS>
+__global__ void __launch_bounds__(kBigThreads, 4) k_direct_inv(DirectArgs a) {
+    __shared__ __attribute__((aligned(16))) double as[kBigE * KS * 64];
+    const LevelView& v = a.v;
     const int nzi = v.nz - 2, nri = v.nr - 2;
-    int h, pl;
-    if (!big_block((nzi + kBigHalf - 1) / kBigHalf, a.np, &h, &pl)) return;  // whole workgroup
+    const int groups = (nzi + 15) / 16;
+    int pl, g0;
+    if (!big_block(groups, a.np, &pl, &g0)) return;
     const int plane = a.p0 + pl;
     if (a.mask && a.mask[plane] == 0) return;
-    const int nrt = (nri + 15) / 16;
-    const int t = threadIdx.x, wave = t >> 6, l = t & 63;
-    const int k0 = h * kBigHalf, ks = (nzi + 3) / 4;
-    const int r = 16 * wave + (l & 15);
-    HalfStage<kBigInvThreads, 1> stage;
-    const int lim[1] = {kBigV};
-    {
-        const double* const src[1] = {a.VT};  // V^T's half [j][64]
-        stage.load(src, lim, k0, t);
-    }
-    // this wave's columns of w (the product's B operands)
-    double wb[kBigSteps];
-    {
-        const double* w = a.w + (size_t)plane * v.pstride;
-        const bool col = wave < nrt && r < nri;
-#pragma unroll
-        for (int s = 0; s < kBigSteps; ++s) {
-            const int j = 4 * s + (l >> 4);
-            wb[s] = col && j < nzi ? w[j * nri + r] : 0.0;
-        }
-    }
-    {
-        double* const dst[1] = {smem};
-        stage.store(dst, lim, t);
-    }
-    __syncthreads();
-    if (wave >= nrt) return;  // after the only barrier
-    // u[k0 + k][r] = sum_j V[k0 + k][j] w[j][r], 4 tiles of 16 rows
-    dbl4 acc[4];
-#pragma unroll
-    for (int kt = 0; kt < 4; ++kt) acc[kt] = dbl4{0.0, 0.0, 0.0, 0.0};
-    const double* vcol = smem + (l >> 4) * kBigHalf + (l & 15);
-    double an[4];
-#pragma unroll
-    for (int kt = 0; kt < 4; ++kt) an[kt] = vcol[16 * kt];
-#pragma unroll
-    for (int s = 0; s < kBigSteps; ++s) {
-        if (s < ks) {
-            double ac[4];
-#pragma unroll
-            for (int kt = 0; kt < 4; ++kt) ac[kt] = an[kt];
-            if (s + 1 < kBigSteps) {
-                const double* vrow = vcol + 4 * (s + 1) * kBigHalf;
-#pragma unroll
-                for (int kt = 0; kt < 4; ++kt) an[kt] = vrow[16 * kt];
-            }
-#pragma unroll
-            for (int kt = 0; kt < 4; ++kt)
-                acc[kt] = __builtin_amdgcn_mfma_f64_16x16x4f64(ac[kt], wb[s], acc[kt], 0, 0, 0);
-        }
-    }
+    const int wave = threadIdx.x >> 6, l = threadIdx.x & 63;
+    const int col = 16 * wave + (l & 15);
+    dbl4 acc[kBigE];
+    product<KS>(a.VT, a.ks, groups, g0, as, a.w + (size_t)plane * v.pstride, nri, nzi, col, 16 * wave < nri, col < nri,
+                l, acc);
+    if (col >= nri) return;
     double* u = a.u + (size_t)plane * v.pstride + v.pitch + 1;
-    if (r < nri) {
 #pragma unroll
-        for (int kt = 0; kt < 4; ++kt)
+    for (int e = 0; e < kBigE; ++e)
 #pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const int k = k0 + 16 * kt + (l >> 4) + 4 * q;
-                if (k < nzi) u[(size_t)k * v.pitch + r] = acc[kt][q];
-            }
-    }
+        for (int q = 0; q < 4; ++q) {
+            const int k = 16 * (g0 + e) + (l >> 4) + 4 * q;
+            if (k < nzi) u[(size_t)k * v.pitch + col] = acc[e][q];
+        }
 }
 
 // Eigenvalues and orthonormal eigenvectors of the symmetric n x n matrix S
@@ -645,27 +425,74 @@ int direct_level(const cylpoisson_plan* p) {
 
 bool direct_active(const cylpoisson_plan* p) { return direct_level(p) > 0; }
 
+// Group size of the one-workgroup form: 16 G interior nodes each way.
+static int direct_g(const HostLevel& H) {
+    const int n = std::max(H.nz, H.nr) - 2;
+    return n <= 16 ? 1 : n <= 32 ? 2 : 4;
+}
+
+int direct_ksteps(const HostLevel& H, bool big) { return big ? (H.nz - 2 + 3) / 4 : 4 * direct_g(H); }
+
+// Operand and factor tables of a level (zero padded), from its eigenvectors
+// V [nzi][nzi], eigenvalues and the modes' shifts lam[0 .. nc - 1].
+void direct_pack(const HostLevel& H, bool big, const std::vector<double>& V, const std::vector<double>& sigma,
+                 const std::vector<double>& lam, int nc, std::vector<double>& Vp, std::vector<double>& VTp,
+                 std::vector<double>& M) {
+    const int nzi = H.nz - 2, nri = H.nr - 2;
+    const int groups = big ? (nzi + 15) / 16 : direct_g(H), ks = direct_ksteps(H, big);
+    Vp.assign((size_t)groups * ks * 64, 0.0);
+    VTp = Vp;
+    for (int g = 0; g < groups; ++g)
+        for (int s = 0; s < ks; ++s)
+            for (int l = 0; l < 64; ++l) {
+                const int row = 16 * g + l % 16, k = 4 * s + l / 16;
+                if (row >= nzi || k >= nzi) continue;
+                const size_t at = ((size_t)g * ks + s) * 64 + l;
+                Vp[at] = V[(size_t)k * nzi + row];   // (V^T)[row][k]
+                VTp[at] = V[(size_t)row * nzi + k];  // V[row][k]
+            }
+    // elimination factors of (T_r(lambda) + sigma_j R_b) w = g along r:
+    // m_i = 1 / (b_i - rw_i c_{i-1}), c_i = re_i m_i
+    const int nseg = big ? kBigSegs : 4 * groups;
+    const size_t per = (size_t)kSegRows * 16 * nseg;
+    M.assign((size_t)nc * groups * per, 0.0);
+    for (int q = 0; q < nc; ++q)
+        for (int j = 0; j < nzi; ++j) {
+            double* out = M.data() + ((size_t)q * groups + j / 16) * per + (size_t)(j % 16) * nseg;
+            double c = 0.0;
+            for (int i = 0; i < nri; ++i) {
+                const int I = i + 1;
+                const double b = H.rw[I] + H.re[I] + lam[q] * H.rm[I] + sigma[j] * H.rb[I];
+                const double mi = 1.0 / (b - H.rw[I] * c);
+                c = H.re[I] * mi;
+                out[(size_t)(i % kSegRows) * 16 * nseg + i / kSegRows] = mi;
+            }
+        }
+}
+
+namespace {
+
+template <int KS>
+hipError_t launch_big(const DirectArgs& a, hipStream_t s) {
+    if constexpr (KS < 32)
+        if (a.ks > KS) return launch_big<KS + 4>(a, s);
+    const int groups = (a.v.nz - 2 + 15) / 16;
+    const int blocks = 8 * ((a.np + 7) / 8) * ((groups + kBigE - 1) / kBigE);
+    k_direct_fwd<KS><<<blocks, kBigThreads, 0, s>>>(a);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    k_direct_inv<KS><<<blocks, kBigThreads, 0, s>>>(a);
+    return hipGetLastError();
+}
+
+}  // namespace
+
 hipError_t launch_direct(cylpoisson_plan* p, hipStream_t s, int p0, int np) {
     const DirectLevel& d = p->dir[p->opt.direct == 2 ? 1 : 0];
     DeviceLevel& L = p->dl[d.level];
     if (np < 0) np = p->nt - p0;
     if (np <= 0) return hipSuccess;
-    const int nzi = L.v.nz - 2, nri = L.v.nr - 2;
-    if (!d.big) {
-        DirectArgs a{};
-        a.v = L.v;
-        a.f = L.f;
-        a.u = L.u;
-        a.V = d.V;
-        a.sigma = d.sigma;
-        a.lam = p->d_lam;
-        a.mask = p->mask_live ? p->d_mask : nullptr;
-        a.p0 = p0;
-        const size_t lds = sizeof(double) * dir_lds_doubles(nzi, nri);
-        k_direct<<<np, kDirThreads, lds, s>>>(a);
-        return hipGetLastError();
-    }
-    BigArgs a{};
+    DirectArgs a{};
     a.v = L.v;
     a.f = L.f;
     a.u = L.u;
@@ -676,26 +503,16 @@ hipError_t launch_direct(cylpoisson_plan* p, hipStream_t s, int p0, int np) {
     a.mask = p->mask_live ? p->d_mask : nullptr;
     a.p0 = p0;
     a.np = np;
-    const int blocks = big_blocks((nzi + kBigHalf - 1) / kBigHalf, np);
-    k_direct_fwd<<<blocks, kBigFwdThreads, sizeof(double) * kBigFwdLds, s>>>(a);
-    k_direct_inv<<<blocks, kBigInvThreads, sizeof(double) * kBigInvLds, s>>>(a);
-    return hipGetLastError();
-}
-
-// The kernels' LDS beyond the default 64 KiB (up to 130 KB for one workgroup
-// per plane, 133 KB for the transform kernel of the two-kernel form), allowed
-// once when a plan is built (a launch under graph capture then needs no host call).
-hipError_t direct_prepare(const HostLevel& H, bool big) {
-    if (big) {
-        static_assert(sizeof(double) * kBigFwdLds <= 160 * 1024, "LDS of k_direct_fwd");
-        static_assert(sizeof(double) * kBigInvLds <= 64 * 1024, "LDS of k_direct_inv");
-        return hipFuncSetAttribute(reinterpret_cast<const void*>(&k_direct_fwd),
-                                   hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
+    a.nc = p->nt / 2 + 1;
+    const HostLevel& H = p->hl[d.level];
+    a.ks = direct_ksteps(H, d.big);
+    if (d.big) return launch_big<4>(a, s);
+    switch (direct_g(H)) {
+        case 1: k_direct<1><<<np, 64, 0, s>>>(a); break;
+        case 2: k_direct<2><<<np, 256, 0, s>>>(a); break;
+        default: k_direct<4><<<np, 1024, 0, s>>>(a); break;
     }
-    const size_t lds = sizeof(double) * dir_lds_doubles(H.nz - 2, H.nr - 2);
-    if (lds <= 64 * 1024) return hipSuccess;
-    return hipFuncSetAttribute(reinterpret_cast<const void*>(&k_direct), hipFuncAttributeMaxDynamicSharedMemorySize,
-                               160 * 1024);
+    return hipGetLastError();
 }
 
 }  // namespace cp

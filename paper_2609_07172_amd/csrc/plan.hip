@@ -681,44 +681,13 @@ cylpoisson_plan* build_plan(cylpoisson_plan* p) {
                     d = p->dir[0];  // the same level, in one workgroup per plane
                     continue;
                 }
-                if (direct_prepare(H, !small) != hipSuccess) {
-                    (void)hipGetLastError();
-                    continue;
-                }
-                std::vector<double> V, sigma;
+                std::vector<double> V, sigma, Vp, VTp, Mf;
                 direct_tables(H, V, sigma);
                 d.big = !small;
-                if (d.big) {
-                    // zero-padded [128][128] copies of V and V^T
-                    const int n = H.nz - 2, m = kDirectBigMax;
-                    std::vector<double> Vp((size_t)m * m, 0.0), VTp((size_t)m * m, 0.0);
-                    for (int k = 0; k < n; ++k)
-                        for (int j = 0; j < n; ++j) {
-                            Vp[(size_t)k * m + j] = V[(size_t)k * n + j];
-                            VTp[(size_t)j * m + k] = V[(size_t)k * n + j];
-                        }
-                    CP_TRY(upload(p, &d.V, Vp));
-                    CP_TRY(upload(p, &d.VT, VTp));
-                    // elimination factors of (T_r(lambda_p) + sigma_j R_b) w = g along r:
-                    // m_i = 1 / (b_i - rw_i c_{i-1}), c_i = re_i m_i, per plane and eigenvector
-                    const int nri = H.nr - 2;
-                    std::vector<double> Mf((size_t)p->nt * m * m, 0.0);
-                    for (int q = 0; q < p->nt; ++q)
-                        for (int j = 0; j < n; ++j) {
-                            double c = 0.0;
-                            for (int i = 0; i < nri; ++i) {
-                                const int I = i + 1;
-                                const double b = H.rw[I] + H.re[I] + p->lam[q] * H.rm[I] + sigma[j] * H.rb[I];
-                                const double mi = 1.0 / (b - H.rw[I] * c);
-                                c = H.re[I] * mi;
-                                Mf[((size_t)q * m + i) * m + j] = mi;
-                            }
-                        }
-                    CP_TRY(upload(p, &d.M, Mf));
-                } else {
-                    CP_TRY(upload(p, &d.V, V));
-                }
-                CP_TRY(upload(p, &d.sigma, sigma));
+                direct_pack(H, d.big, V, sigma, p->lam, Ntheta / 2 + 1, Vp, VTp, Mf);
+                CP_TRY(upload(p, &d.V, Vp));
+                CP_TRY(upload(p, &d.VT, VTp));
+                CP_TRY(upload(p, &d.M, Mf));
                 d.level = l;
             }
         }
