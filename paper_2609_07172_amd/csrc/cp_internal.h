@@ -14,6 +14,8 @@ namespace cp {
 
 // Vacuum permittivity, CODATA 2018 (F/m).
 constexpr double kEps0 = 8.8541878128e-12;
+// Rows of zeros around a level's row table: more than a pass looks up outside the level.
+constexpr int kRowPad = 16;
 
 // One multigrid level as seen by a kernel.  Plane arrays are
 // [Ntheta][nz][pitch] doubles, node (k, i) of plane p at p*pstride + k*pitch + i;
@@ -66,6 +68,8 @@ struct DeviceLevel {
     // or everywhere on a stretched mesh)
     int reg_lo = 1, reg_hi = 1;
     double zc0 = 0, zs0 = 0, zn0 = 0;
+    // {zc, zs, zn, 0} of row k at zrow[4 k], kRowPad rows of zeros on both sides
+    const double* zrow = nullptr;
 };
 
 // FP32 copies of a level's iterate buffers and right-hand side, used by the

@@ -27,7 +27,9 @@ hipError_t launch_pass(int nu, bool fine, const Shape& sh, const PassArgs<double
     if (nu != kNu) return launch_other(KIND, nu, fine, sh, a, np, s);
     switch (sh.coef) {
         case kOneBand: return launch_zc<double, kNu, KIND, kOneBand>(fine, sh, a, np, s);
-        case kSomeRows: return launch_zc<double, kNu, KIND, kSomeRows>(fine, sh, a, np, s);
+        case kSomeRows:
+            if constexpr (KIND != kMerge) return launch_zc<double, kNu, KIND, kSomeRows>(fine, sh, a, np, s);
+            return hipErrorInvalidValue;
         default: return launch_zc<double, kNu, KIND, kRowTables>(fine, sh, a, np, s);
     }
 }

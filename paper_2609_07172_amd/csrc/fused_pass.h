@@ -65,6 +65,7 @@ struct PassArgs {
     T* fc;               // down: coarse right-hand side
     const T* ec;         // up: coarse correction
     const double* lam;
+    const double* zrow;  // {zc, zs, zn, 0} of every row, kRowPad rows of zeros before row 0 and after the last
     int rc;              // the coarse level is coarsened in r
     int reg_lo, reg_hi;  // rows reg_lo <= y < reg_hi share the axial coefficients (zc0, zs0, zn0)
     double* partial;     // up: per (plane, chunk, strip) sum of squared residuals, or nullptr
@@ -80,13 +81,26 @@ struct PassArgs {
 enum PassKind { kDownZero = 0, kDownRing = 1, kDownFull = 2, kDownPro = 3, kUp = 4, kMerge = 5 };
 
 // Where a level's coefficients come from.  kOneBand: every interior row is in
-// the regular band, whose coefficients stay in registers.  kSomeRows: the rows
-// outside the band (next to a face) form theirs from the tables where they are
-// used, in steps of their own, which raises the registers of the whole pass.
-// kRowTables, for levels with few rows in the band (stretched meshes): every
-// row's coefficients come from its tables in all steps, and each row's two
-// inverse diagonals are formed once, when the row is consumed, and stay in
-// registers with the row.
+// the regular band, whose coefficients stay in registers.  kSomeRows: the few
+// rows outside the band (next to a face) form theirs from the tables where
+// they are used, in steps of their own.  kRowTables: every row's coefficients
+// come from its tables in all steps; each row's two inverse diagonals are
+// formed once, when the row is consumed, and stay in LDS (a ring of rows, 16 KB
+// a wavefront: each lane reads its own, and as registers they and their moves
+// would leave one wavefront a SIMD), and the row tables are four doubles a row
+// with padding on both sides, so that a step reads them in a few scalar loads
+// without bounds.
+//
+// Steps in the band cost less, a row outside it about a microsecond: with two
+// rows outside (400 x 128 x 512, cells) the finest up pass takes 150 us as
+// kSomeRows and 172 us as kRowTables, at 201 x 128 x 257 the down and up pass
+// with one 36 and 40 us against 47 and 43, but with 54 rows outside 109 and 80
+// against 51 and 46.  A merged pass of kSomeRows does not fit two wavefronts a
+// SIMD and is slower on every mesh (129 x 64 x 129: 547 us the solve, 472 as
+// kRowTables).
+// Stretched 400 x 128 x 512: merged pass 205 us (inverse diagonals in
+// registers and the tables row by row: 358, one wavefront a SIMD), level 1 down
+// and up 47 and 43 us (57 and 42).
 enum CoefMode { kOneBand = 0, kSomeRows = 1, kRowTables = 2 };
 
 struct Shape {
@@ -103,8 +117,9 @@ namespace {
 // Lanes of a strip that no neighbouring strip owns, for nu sweeps.
 constexpr int strip_step(int nu) { return 62 - 2 * nu; }
 
-constexpr int kPassWaves = 2048;  // wavefronts of an automatic launch shape: two per SIMD
+constexpr int kPassWaves = 2048;  // wavefronts of an automatic launch shape at two per SIMD
 constexpr int kMinChunk = 4;      // rows per chunk at least
+constexpr int kFewRows = 4;       // rows outside the band that kSomeRows serves: two next to each face
 
 // ---- buffer access: a scalar base and range, 32-bit lane and row offsets ----
 // Accesses beyond the range read zero and write nothing, so a lane or row is
@@ -173,6 +188,8 @@ __device__ __forceinline__ T from_lane(T x) {
 // Row tables are read with a wavefront-uniform index and never written by a
 // pass: scalar loads from the constant address space.
 typedef const __attribute__((address_space(4))) double* CTab;
+typedef double ZRow __attribute__((ext_vector_type(4)));
+typedef const __attribute__((address_space(4))) ZRow* CRow;
 __device__ __forceinline__ CTab ctab(const double* p) { return (CTab)(unsigned long long)p; }
 
 // What a pass reads as its input iterate: nothing (zero with a zero ring), the
@@ -194,6 +211,8 @@ struct Pass {
     // outputs of a step's rows: none of them in the chunk, all, or checked
     static constexpr int kNone = 0, kAll = 1, kCheck = 2;
 
+    static_assert(H + 3 <= kRowPad, "rows a pass looks up beyond the level's");
+
     const PassArgs<T>& a;
     int p, za, zb, s, lend, nz;
     double lam;
@@ -203,12 +222,15 @@ struct Pass {
     double rw[ROWS ? 2 : 1], re[ROWS ? 2 : 1], rb[ROWS ? 2 : 1], rm[ROWS ? 2 : 1];  // radial tables
     int ic[2];                          // the columns, or an interior one in place of a column outside
     rsrc_t ru, rf, ro, rc_, re_;
+    CRow zrow;
     CTab zct, zst, znt, pwl, pwr, rwm, rwp;
     unsigned rowb, crowb;               // bytes per row, fine and coarse
     unsigned voff, vring, vout, vec_, vfc;  // lane offsets: loads, ring-only loads, u store, e load, fc store
     T w1a, w1b, w2a, w2b;               // radial prolongation of the two columns from the pair (e_a, e_b)
     T wrm, wrp;                         // radial restriction at the coarse column under 2t
-    T u[N][2], f[N][2], iv[ROWS ? N : 1][2];
+    T u[N][2], f[N][2];
+    static constexpr int kRing = N <= 8 ? 8 : N <= 16 ? 16 : 32;
+    T* ivl;                             // inverse diagonals of the rows held, [kRing][2][64]: row y in y % kRing
     Pair<T> pu[U], pf[U], pe[U];
     T ea[2];                            // radially interpolated coarse row at or below the consumed row
     T rs[2], r1[2];                     // restriction: the sum so far, the row below the next coarse row
@@ -217,8 +239,14 @@ struct Pass {
     __device__ __forceinline__ explicit Pass(const PassArgs<T>& args) : a(args) {}
 
     __device__ __forceinline__ bool interior(int y) const { return y >= 1 && y <= nz - 2; }
-    __device__ __forceinline__ bool regular(int y) const { return y >= a.reg_lo && y < a.reg_hi; }
+    // rows that the band's coefficients serve; rows outside the interior keep
+    // their values whatever the coefficients
+    __device__ __forceinline__ bool regular(int y) const { return (y >= a.reg_lo && y < a.reg_hi) || !interior(y); }
     __device__ __forceinline__ int row(int y) const { return min(max(y, 0), nz - 1); }
+
+    __device__ __forceinline__ unsigned ivpos(int y, int c) const {
+        return ((unsigned)(y & (kRing - 1)) * 2 + c) * 64 + threadIdx.x;
+    }
 
     // Radial interpolation of a loaded coarse pair to the lane's two columns.
     __device__ __forceinline__ void interpolate(const Pair<T>& e, T (&o)[2]) const {
@@ -285,6 +313,7 @@ struct Pass {
         voff = c1 < v.nr ? (unsigned)(c1 * sizeof(T)) : kOff;
         vring = any && act[0] && act[1] ? kOff : voff;
         vout = own && any ? voff : kOff;
+        zrow = (CRow)(unsigned long long)a.zrow;
         zct = ctab(v.zc);
         zst = ctab(v.zs);
         znt = ctab(v.zn);
@@ -314,7 +343,6 @@ struct Pass {
 #pragma unroll
             for (int c = 0; c < 2; ++c) {
                 u[k][c] = f[k][c] = T(0);
-                if (ROWS) iv[k][c] = T(0);
             }
         rs[0] = rs[1] = r1[0] = r1[1] = T(0);
         acc = 0.0;
@@ -377,11 +405,10 @@ struct Pass {
         f[B][0] = act[0] ? pf[J].a : T(0);  // ring entries of f are the caller's and not read
         f[B][1] = act[1] ? pf[J].b : T(0);
         if constexpr (ROWS) {
-            const int y = row(x);
-            const double zc = zct[y], zs = zst[y], zn = znt[y];
+            const ZRow z = zrow[x];
 #pragma unroll
             for (int c = 0; c < 2; ++c)
-                iv[B][c] = (T)make_coef(rw[c], re[c], rb[c], rm[c], zc, zs, zn, lam).invd;
+                ivl[ivpos(x, c)] = (T)make_coef(rw[c], re[c], rb[c], rm[c], z.x, z.y, z.z, lam).invd;
         }
         issue<J>(x + U);
     }
@@ -391,10 +418,10 @@ struct Pass {
     __device__ __forceinline__ CoefT<T> coef(int y) const {
         if (CM == kBand) return cu[C];
         if constexpr (ROWS) {
-            const int r = row(y);
-            Coef c = make_coef_products(rw[C], re[C], rb[C], rm[C], zct[r], zst[r], znt[r], lam);
+            const ZRow z = zrow[y];
+            Coef c = make_coef_products(rw[C], re[C], rb[C], rm[C], z.x, z.y, z.z, lam);
             CoefT<T> o = coef_as<T>(c);
-            o.invd = iv[K][C];
+            o.invd = ivl[ivpos(y, C)];
             return o;
         } else {
             const int r = row(y), i = ic[C];
@@ -427,6 +454,9 @@ struct Pass {
             rne = from_lane<false>(u[R][0]);
         }
         consume<J, PRED>(x);
+        // each step loads its rows' tables: kept from step to step they would
+        // be more scalar registers than there are
+        if (ROWS) __asm__ volatile("" : "+s"(zrow));
         sweeps<0, J, PRED, CM>(x, nb);
         const int yf = x - H;  // final now
         if (OUT == kAll || (OUT == kCheck && yf >= za && yf < zb))
@@ -519,7 +549,6 @@ struct Pass {
             for (int c = 0; c < 2; ++c) {
                 u[k][c] = u[k - U][c];
                 f[k][c] = f[k - U][c];
-                if (ROWS) iv[k][c] = iv[k - U][c];
             }
     }
 
@@ -537,6 +566,10 @@ struct Pass {
 
     __device__ __forceinline__ void run() {
         if (!setup()) return;
+        if constexpr (ROWS) {
+            __shared__ T ring[kRing * 2 * 64];
+            ivl = ring;
+        }
         issue<0>(s);
         issue<1>(s + 1);
         if (XP) {
@@ -596,7 +629,7 @@ using PassOf = Pass<T, NU, kind_input(KIND), (KIND >= kDownPro), (KIND != kUp), 
 
 // Two wavefronts per SIMD (up to 256 registers) where that spills nothing or
 // little, else one.
-constexpr int pass_waves(int nu, int coef) { return nu <= 3 || (nu == 4 && coef == kOneBand) ? 2 : 1; }
+constexpr int pass_waves(int nu, int coef) { return nu <= 3 || (nu == 4 && coef != kSomeRows) ? 2 : 1; }
 
 template <typename T, int NU, int KIND, bool ZC, int COEF>
 __global__ void __launch_bounds__(64, pass_waves(NU, COEF)) k_pass(PassArgs<T> a) {
@@ -639,12 +672,14 @@ Shape pass_shape(const cylpoisson_plan* p, int l, int nu, bool down, bool merge 
     const DeviceLevel& L = p->dl[l];
     Shape sh;
     sh.nstrips = strips_of(L.v.nr, nu);
+    const int outside = L.v.nz - 2 - (L.reg_hi - L.reg_lo);
+    sh.coef = outside <= 0 ? kOneBand : nu >= 4 || outside > kFewRows ? kRowTables : kSomeRows;
     const int rows = L.v.nz - 2;
     int chunk = merge ? p->opt.chunk_rows_merge : l == 0 ? p->opt.chunk_rows : p->opt.chunk_rows_coarse;
     const bool automatic = chunk <= 0;
     if (automatic) {
-        // as many chunks as keep every wavefront resident at once (two per SIMD)
-        const int per_plane = std::max(1, kPassWaves / (p->nt * sh.nstrips));
+        // as many chunks as keep every wavefront resident at once
+        const int per_plane = std::max(1, kPassWaves * pass_waves(nu, sh.coef) / 2 / (p->nt * sh.nstrips));
         chunk = std::max(kMinChunk, (rows + per_plane - 1) / per_plane);
     }
     // an up pass keeps one norm partial per wavefront: at most 64 a plane
@@ -660,10 +695,6 @@ Shape pass_shape(const cylpoisson_plan* p, int l, int nu, bool down, bool merge 
     sh.nchunks = (rows + chunk - 1) / chunk;
     sh.per_plane = sh.nchunks * sh.nstrips;
     sh.zc = p->dl[l + 1].v.nz < L.v.nz;
-    // every interior row in the band, most of them, or few (a stretched mesh)
-    sh.coef = L.reg_lo <= 1 && L.reg_hi >= L.v.nz - 1 ? kOneBand
-              : 2 * (L.reg_hi - L.reg_lo) < L.v.nz - 2 ? kRowTables
-                                                       : kSomeRows;
     return sh;
 }
 
@@ -678,6 +709,7 @@ PassArgs<T> make_args(const cylpoisson_plan* p, int l, const Shape& sh, int p0, 
     a.tr = L.tr;
     a.tz = L.tz;
     a.lam = p->d_lam;
+    a.zrow = L.zrow;
     a.rc = C.v.nr < L.v.nr ? 1 : 0;
     a.reg_lo = L.reg_lo;
     a.reg_hi = L.reg_hi;

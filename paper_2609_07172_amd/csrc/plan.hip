@@ -620,6 +620,18 @@ cylpoisson_plan* build_plan(cylpoisson_plan* p) {
             D.v.zc = zc;
             D.v.zs = zs;
             D.v.zn = zn;
+            {
+                std::vector<double> rows((size_t)(H.nz + 2 * kRowPad) * 4, 0.0);
+                for (int k = 0; k < H.nz; ++k) {
+                    double* e = &rows[(size_t)(k + kRowPad) * 4];
+                    e[0] = H.zc[k];
+                    e[1] = H.zs[k];
+                    e[2] = H.zn[k];
+                }
+                double* d;
+                CP_TRY(upload(p, &d, rows));
+                D.zrow = d + kRowPad * 4;
+            }
             if (l + 1 < nl) {
                 int *a, *b, *c, *d;
                 double *w1, *w2, *w3, *w4, *w5, *w6, *w7, *w8;
