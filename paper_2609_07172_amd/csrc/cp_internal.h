@@ -315,8 +315,11 @@ hipError_t launch_norm_final(const double* partial, int nb, int nt, double* out,
 hipError_t launch_line_sweep(const DeviceLevel& L, int nt, const double* lam, double* u, const double* f,
                              double* scratch, bool along_r, int color, hipStream_t s);
 hipError_t launch_init_ring(const DeviceLevel& L, int nt, const cylpoisson_bc& bc, hipStream_t s);
-hipError_t launch_rhs_norms(const DeviceLevel& L, int nt, const double* lam, const double* u,
-                            const double* f, double* partial, double* norms_out, hipStream_t s);
+// per-plane sums of squares of the residual f - A u (r_norms) and of the
+// right-hand side, the residual of u's ring around a zero interior (b_norms);
+// either may be null (the interior of u is read for r_norms only)
+hipError_t launch_norms(const DeviceLevel& L, int nt, const double* lam, const double* u, const double* f,
+                        double* partial, double* r_norms, double* b_norms, hipStream_t s);
 hipError_t launch_copy_ring(const DeviceLevel& L, int nt, const double* src, double* dst,
                             hipStream_t s);
 // FP64 refinement step of the mixed-precision solve on the finest level:

@@ -146,9 +146,7 @@ void collect_timing(cylpoisson_plan* p) {
 hipError_t residual_norms(cylpoisson_plan* p, int slot, hipStream_t s) {
     Timed tm(p, kOther, s);
     DeviceLevel& L = p->dl[0];
-    hipError_t e = launch_residual(L, p->nt, p->d_lam, L.u, L.f, L.r, s);
-    if (e != hipSuccess) return e;
-    return launch_plane_norms(L, p->nt, L.r, p->d_partial, p->d_norms + (size_t)slot * p->nt, s);
+    return launch_norms(L, p->nt, p->d_lam, L.u, L.f, p->d_partial, p->d_norms + (size_t)slot * p->nt, nullptr, s);
 }
 
 // `sweeps` smoothing sweeps on a level by the one-kernel-per-colour path: point
@@ -696,12 +694,10 @@ int run_cycles(cylpoisson_plan* p, double tol, hipStream_t s, bool ring_only, bo
         if (fmg) {
             // the right-hand side norms are in slot 0 already (launched with the start)
         } else if (ring_only) {
-            CP_HIP(launch_rhs_norms(L, nt, p->d_lam, L.u, L.f, p->d_partial, p->d_norms, s));
+            CP_HIP(launch_norms(L, nt, p->d_lam, L.u, L.f, p->d_partial, nullptr, p->d_norms, s));
         } else {
-            CP_HIP(residual_norms(p, 0, s));
-            if (warm)
-                CP_HIP(launch_rhs_norms(L, nt, p->d_lam, L.u, L.f, p->d_partial,
-                                        p->d_norms + (size_t)kRhsSlot * nt, s));
+            CP_HIP(launch_norms(L, nt, p->d_lam, L.u, L.f, p->d_partial, p->d_norms,
+                                warm ? p->d_norms + (size_t)kRhsSlot * nt : nullptr, s));
         }
     }
     CheckCtl k;
@@ -833,8 +829,8 @@ int run_mixed(cylpoisson_plan* p, double tol, hipStream_t s, double** result, bo
             Timed tm(p, kOther, s);
             if (it == 0 && warm) {
                 // right-hand side norms, then the residual of the given iterate
-                CP_HIP(launch_rhs_norms(L, nt, p->d_lam, ucur, L.f, p->d_partial,
-                                        p->d_norms + (size_t)kRhsSlot * nt, s));
+                CP_HIP(launch_norms(L, nt, p->d_lam, ucur, L.f, p->d_partial, nullptr,
+                                    p->d_norms + (size_t)kRhsSlot * nt, s));
                 CP_HIP(launch_refine(L, nt, p->d_lam, ucur, nullptr, nullptr, L.f, E.f, p->d_partial,
                                      p->d_norms, s));
             } else if (it == 0) {
@@ -1021,7 +1017,7 @@ int run_learned(cylpoisson_plan* p, double tol, hipStream_t s) {
     const int nt = p->nt;
     DeviceLevel& L = p->dl[0];
     CP_HIP(krylov_reserve(p, p->opt.krylov_restart));
-    CP_HIP(launch_rhs_norms(L, nt, p->d_lam, L.u, L.f, p->d_partial, p->d_norms, s));
+    CP_HIP(launch_norms(L, nt, p->d_lam, L.u, L.f, p->d_partial, nullptr, p->d_norms, s));
     CP_HIP(hipMemcpyAsync(p->h_norms, p->d_norms, nt * sizeof(double), hipMemcpyDeviceToHost, s));
     CP_HIP(hipStreamSynchronize(s));
     const double b2 = weighted(p, p->h_norms);
@@ -1392,11 +1388,10 @@ int cylpoisson_apply(cylpoisson_plan* p, const double* phi, double* rho_out, voi
     if (st != CYLPOISSON_OK) return st;
     hipStream_t s = static_cast<hipStream_t>(stream);
     DeviceLevel& L = p->dl[0];
-    CP_HIP(transform(p, false, phi, L.r, nullptr, s));
-    CP_HIP(launch_apply(L, p->nt, p->d_lam, L.r, p->d_inv_s, p->d_tmp, s));
+    // every solve writes all of f before it reads any
+    CP_HIP(transform(p, false, phi, L.f, nullptr, s));
+    CP_HIP(launch_apply(L, p->nt, p->d_lam, L.f, p->d_inv_s, p->d_tmp, s));
     CP_HIP(transform(p, true, p->d_tmp, rho_out, nullptr, s));
-    // the residual scratch must keep a zero ring for the solver
-    CP_HIP(launch_zero(L.r, (long long)p->nt * L.v.pstride, s));
     return CYLPOISSON_OK;
 }
 
