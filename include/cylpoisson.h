@@ -273,13 +273,14 @@ void cylpoisson_plan_destroy(cylpoisson_plan* plan);
  *                    tridiagonal solve per eigenvector, and the inverse transform.
  *                    1 = the first level from 1 on, at or above the bottom kernel's
  *                    first level, with at most 128 interior nodes each way; a level
- *                    above 64 nodes in either direction runs two kernels with FP64
- *                    matrix-core transforms and two workgroups per plane, using the
- *                    level's residual array as scratch.  2 = the first such level with
- *                    at most 64 each way, one workgroup per plane with everything in
- *                    LDS.  0 = off: the V-cycle goes down to the bottom kernel.  Used
- *                    by every FP64 V-cycle, the full-multigrid start included; the
- *                    FP32 inner cycles of "precision" 32 keep the bottom kernel.
+ *                    above 64 nodes in either direction runs two kernels, several
+ *                    workgroups per plane, using the level's residual array as
+ *                    scratch.  2 = the first such level with at most 64 each way, one
+ *                    workgroup per plane with everything between the transforms in
+ *                    LDS.  The transforms run on the FP64 matrix cores.  0 = off: the
+ *                    V-cycle goes down to the bottom kernel.  Used by every V-cycle,
+ *                    the full-multigrid start and the FP32 inner cycles of
+ *                    "precision" 32 included (there in FP64 on FP32 level values).
  *                    Ignored where no level qualifies (0 .. 2; default 1)
  *   "graph"          1 = the cycles from one convergence check to the next are
  *                    captured once into a HIP graph and replayed (single plane

@@ -402,6 +402,8 @@ int direct_level(const cylpoisson_plan* p);
 bool direct_active(const cylpoisson_plan* p);
 // u = A^-1 f on the direct level's interior (ring untouched), planes p0 .. p0 + np - 1
 hipError_t launch_direct(cylpoisson_plan* p, hipStream_t s, int p0 = 0, int np = -1);
+// the same solve in FP64 on the FP32 level's right-hand side and answer
+hipError_t launch_direct32(cylpoisson_plan* p, hipStream_t s, int p0 = 0, int np = -1);
 
 // ---- fused passes (fused.hip) ----
 bool fused_supported(const cylpoisson_plan* p, int l);
@@ -446,5 +448,9 @@ void drop_graphs(cylpoisson_plan* p);
 // Every level above the bottom kernel has fused passes (plan.hip).
 bool mixed_supported(const cylpoisson_plan* p);
 hipError_t fused_up32(cylpoisson_plan* p, int l, hipStream_t s, int p0 = 0, int np = -1);
+// the finest level's merged pass in FP32 (two sweeps of either kind): up pass
+// and prolongation of one inner cycle, down pass of the next (all planes)
+bool fused_merge32_ok(const cylpoisson_plan* p);
+hipError_t fused_merge32(cylpoisson_plan* p, hipStream_t s);
 
 }  // namespace cp

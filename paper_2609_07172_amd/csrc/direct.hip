@@ -57,11 +57,12 @@ typedef double dbl4 __attribute__((ext_vector_type(4)));
 
 constexpr int kSegRows = 4;  // rows of an elimination segment (one lane)
 
+template <typename T>
 struct DirectArgs {
     LevelView v;          // the direct level
-    const double* f;      // right-hand side (the level's f)
-    double* u;            // answer (the level's u; its ring stays zero)
-    double* w;            // two-kernel form: w [nzi][nri] of each plane between the kernels
+    const T* f;           // right-hand side (the level's f)
+    T* u;                 // answer (the level's u; its ring stays zero)
+    double* w;            // two-kernel form: w between the kernels, row j of a plane in its interior row j
     const double* V;      // A operands of V^T, [group][k-step][lane]
     const double* VT;     // A operands of V
     const double* M;      // elimination factors, [mode][group][row of segment][chain and segment]
@@ -147,8 +148,8 @@ __device__ __forceinline__ void eliminate(const SegTables& tb, double (&g)[kSegR
 // One workgroup per plane, up to 16 G interior nodes each way: G x G wavefronts,
 // wavefront (g, c) forms the 16 x 16 tile of group g and radial columns 16 c of
 // each transform, and a lane one segment of one eigenvector between them.
-template <int G>
-__global__ void __launch_bounds__(64 * G * G) k_direct(DirectArgs a) {
+template <int G, typename T>
+__global__ void __launch_bounds__(64 * G * G) k_direct(DirectArgs<T> a) {
     constexpr int N = 16 * G, NSEG = 4 * G, KS = 4 * G, LD = N + 1;
     __shared__ double gs[N * LD];
     const LevelView& v = a.v;
@@ -163,7 +164,7 @@ __global__ void __launch_bounds__(64 * G * G) k_direct(DirectArgs a) {
 #pragma unroll
     for (int s = 0; s < KS; ++s) {
         const int k = 4 * s + kr;
-        fb[s] = in && k < nzi ? a.f[base + (size_t)k * v.pitch + col] : 0.0;
+        fb[s] = in && k < nzi ? (double)a.f[base + (size_t)k * v.pitch + col] : 0.0;
         va[s] = a.V[((size_t)grp * KS + s) * 64 + l];
     }
     const int chain = t / NSEG, seg = t % NSEG;
@@ -196,7 +197,7 @@ __global__ void __launch_bounds__(64 * G * G) k_direct(DirectArgs a) {
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
         const int k = 16 * grp + kr + 4 * q;
-        if (k < nzi) a.u[base + (size_t)k * v.pitch + col] = acc[q];
+        if (k < nzi) a.u[base + (size_t)k * v.pitch + col] = (T)acc[q];
     }
 }
 
@@ -223,9 +224,9 @@ __device__ __forceinline__ bool big_block(int groups, int np, int* plane, int* g
 // in registers and the A operands in LDS (`as`, kBigE ks 64 values), where
 // every wavefront reads them, all loaded at once.  Every thread of the
 // workgroup calls it; wavefronts past the last column tile (!on) only stage.
-template <int KS>
+template <int KS, typename S>
 __device__ __forceinline__ void product(const double* __restrict__ A, int ks, int groups, int g0, double* as,
-                                        const double* __restrict__ src, size_t pitch, int n, int col, bool on, bool in,
+                                        const S* __restrict__ src, size_t pitch, int n, int col, bool on, bool in,
                                         int l, dbl4 (&acc)[kBigE]) {
     constexpr int NA = (kBigE * KS * 32 + kBigThreads - 1) / kBigThreads;  // 16-byte pieces per thread
     const double2* ag = reinterpret_cast<const double2*>(A + (size_t)g0 * ks * 64);
@@ -238,7 +239,7 @@ __device__ __forceinline__ void product(const double* __restrict__ A, int ks, in
 #pragma unroll
     for (int s = 0; s < KS; ++s) {
         const int k = 4 * s + (l >> 4);
-        fb[s] = in && k < n ? src[(size_t)k * pitch + col] : 0.0;
+        fb[s] = in && k < n ? (double)src[(size_t)k * pitch + col] : 0.0;
     }
 #pragma unroll
     for (int i = 0; i < NA; ++i)
@@ -259,8 +260,8 @@ __device__ __forceinline__ void product(const double* __restrict__ A, int ks, in
 }
 
 // Transform and eliminations of 32 eigenvectors.
-template <int KS>
-__global__ void __launch_bounds__(kBigThreads, 4) k_direct_fwd(DirectArgs a) {
+template <int KS, typename T>
+__global__ void __launch_bounds__(kBigThreads, 4) k_direct_fwd(DirectArgs<T> a) {
     constexpr int LD = kDirectBigMax + 1;
     __shared__ double gs[16 * kBigE * LD];
     __shared__ __attribute__((aligned(16))) double as[kBigE * KS * 64];
@@ -301,7 +302,7 @@ __global__ void __launch_bounds__(kBigThreads, 4) k_direct_fwd(DirectArgs a) {
         }
         eliminate<kBigSegs>(tb[e], g, seg);
         if (j < nzi) {
-            double* wout = a.w + (size_t)plane * v.pstride + (size_t)j * nri + seg * kSegRows;
+            double* wout = a.w + (size_t)plane * v.pstride + (size_t)(j + 1) * v.pitch + 1 + seg * kSegRows;
 #pragma unroll
             for (int u = 0; u < kSegRows; ++u)
                 if (seg * kSegRows + u < nri) wout[u] = g[u];
@@ -310,8 +311,8 @@ __global__ void __launch_bounds__(kBigThreads, 4) k_direct_fwd(DirectArgs a) {
 }
 
 // Inverse transform of 32 axial rows.
-template <int KS>
-__global__ void __launch_bounds__(kBigThreads, 4) k_direct_inv(DirectArgs a) {
+template <int KS, typename T>
+__global__ void __launch_bounds__(kBigThreads, 4) k_direct_inv(DirectArgs<T> a) {
     __shared__ __attribute__((aligned(16))) double as[kBigE * KS * 64];
     const LevelView& v = a.v;
     const int nzi = v.nz - 2, nri = v.nr - 2;
@@ -323,16 +324,16 @@ __global__ void __launch_bounds__(kBigThreads, 4) k_direct_inv(DirectArgs a) {
     const int wave = threadIdx.x >> 6, l = threadIdx.x & 63;
     const int col = 16 * wave + (l & 15);
     dbl4 acc[kBigE];
-    product<KS>(a.VT, a.ks, groups, g0, as, a.w + (size_t)plane * v.pstride, nri, nzi, col, 16 * wave < nri, col < nri,
-                l, acc);
+    product<KS>(a.VT, a.ks, groups, g0, as, a.w + (size_t)plane * v.pstride + v.pitch + 1, v.pitch, nzi, col,
+                16 * wave < nri, col < nri, l, acc);
     if (col >= nri) return;
-    double* u = a.u + (size_t)plane * v.pstride + v.pitch + 1;
+    T* u = a.u + (size_t)plane * v.pstride + v.pitch + 1;
 #pragma unroll
     for (int e = 0; e < kBigE; ++e)
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
             const int k = 16 * (g0 + e) + (l >> 4) + 4 * q;
-            if (k < nzi) u[(size_t)k * v.pitch + col] = acc[e][q];
+            if (k < nzi) u[(size_t)k * v.pitch + col] = (T)acc[e][q];
         }
 }
 
@@ -472,10 +473,10 @@ void direct_pack(const HostLevel& H, bool big, const std::vector<double>& V, con
 
 namespace {
 
-template <int KS>
-hipError_t launch_big(const DirectArgs& a, hipStream_t s) {
+template <int KS, typename T>
+hipError_t launch_big(const DirectArgs<T>& a, hipStream_t s) {
     if constexpr (KS < 32)
-        if (a.ks > KS) return launch_big<KS + 4>(a, s);
+        if (a.ks > KS) return launch_big<KS + 4, T>(a, s);
     const int groups = (a.v.nz - 2 + 15) / 16;
     const int blocks = 8 * ((a.np + 7) / 8) * ((groups + kBigE - 1) / kBigE);
     k_direct_fwd<KS><<<blocks, kBigThreads, 0, s>>>(a);
@@ -485,17 +486,16 @@ hipError_t launch_big(const DirectArgs& a, hipStream_t s) {
     return hipGetLastError();
 }
 
-}  // namespace
-
-hipError_t launch_direct(cylpoisson_plan* p, hipStream_t s, int p0, int np) {
+template <typename T>
+hipError_t launch_direct_t(cylpoisson_plan* p, const T* f, T* u, hipStream_t s, int p0, int np) {
     const DirectLevel& d = p->dir[p->opt.direct == 2 ? 1 : 0];
-    DeviceLevel& L = p->dl[d.level];
+    const DeviceLevel& L = p->dl[d.level];
     if (np < 0) np = p->nt - p0;
     if (np <= 0) return hipSuccess;
-    DirectArgs a{};
+    DirectArgs<T> a{};
     a.v = L.v;
-    a.f = L.f;
-    a.u = L.u;
+    a.f = f;
+    a.u = u;
     a.w = L.r;
     a.V = d.V;
     a.VT = d.VT;
@@ -506,13 +506,25 @@ hipError_t launch_direct(cylpoisson_plan* p, hipStream_t s, int p0, int np) {
     a.nc = p->nt / 2 + 1;
     const HostLevel& H = p->hl[d.level];
     a.ks = direct_ksteps(H, d.big);
-    if (d.big) return launch_big<4>(a, s);
+    if (d.big) return launch_big<4, T>(a, s);
     switch (direct_g(H)) {
-        case 1: k_direct<1><<<np, 64, 0, s>>>(a); break;
-        case 2: k_direct<2><<<np, 256, 0, s>>>(a); break;
-        default: k_direct<4><<<np, 1024, 0, s>>>(a); break;
+        case 1: k_direct<1, T><<<np, 64, 0, s>>>(a); break;
+        case 2: k_direct<2, T><<<np, 256, 0, s>>>(a); break;
+        default: k_direct<4, T><<<np, 1024, 0, s>>>(a); break;
     }
     return hipGetLastError();
+}
+
+}  // namespace
+
+hipError_t launch_direct(cylpoisson_plan* p, hipStream_t s, int p0, int np) {
+    const DeviceLevel& L = p->dl[direct_level(p)];
+    return launch_direct_t<double>(p, L.f, L.u, s, p0, np);
+}
+
+hipError_t launch_direct32(cylpoisson_plan* p, hipStream_t s, int p0, int np) {
+    const DeviceLevel32& L = p->dl32[direct_level(p)];
+    return launch_direct_t<float>(p, L.f, L.u, s, p0, np);
 }
 
 }  // namespace cp
