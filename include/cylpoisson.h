@@ -361,14 +361,15 @@ int cylpoisson_get_stats(const cylpoisson_plan* plan, cylpoisson_stats* out);
 /* Plan geometry and hierarchy.  Returns OK or EINVAL. */
 int cylpoisson_get_info(const cylpoisson_plan* plan, cylpoisson_info* out);
 
-/* Apply the discrete 3-D operator through the mode path:
+/* Apply the discrete 3-D operator:
  *     rho_out = (A_full phi) / s_q   at interior nodes,  0 at boundary nodes,
  * where A_full is the seven-point cell balance of App. A plus the azimuthal
  * three-point term (the left-hand side of Eq. full_finite_volume_row with the
  * boundary nodes of phi as neighbours) and s_q = r_i dr_i dz_k / eps0 with the
- * control-volume widths dr_i, dz_k.  So solving with rho_out returns phi.  Computed as DFT, per-plane
- * A_0 + lambda_m M (Eq. shifted_operator_family), inverse DFT.  Enqueues on
- * stream without synchronising.  Returns OK, EINVAL, EDEVICE or EHIP. */
+ * control-volume widths dr_i, dz_k.  So solving with rho_out returns phi.  Evaluated on the
+ * node array: the modes' shifts lambda_m are the eigenvalues of the azimuthal
+ * term (Eq. shifted_operator_family), so no transform is needed.  rho_out may
+ * be or overlap phi.  Enqueues on stream without synchronising.  Returns OK, EINVAL, EDEVICE or EHIP. */
 int cylpoisson_apply(cylpoisson_plan* plan, const double* phi, double* rho_out, void* stream);
 
 /* Forward azimuthal DFT of a node array into planes (convention above).

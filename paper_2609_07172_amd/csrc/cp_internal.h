@@ -307,8 +307,10 @@ hipError_t launch_coarse_solve(const DeviceLevel& L, int nt, const double* lam, 
                                int n, const double* f, double* u, hipStream_t s);
 hipError_t launch_plane_norms(const DeviceLevel& L, int nt, const double* r, double* partial,
                               double* norms_out, hipStream_t s);
-hipError_t launch_apply(const DeviceLevel& L, int nt, const double* lam, const double* u,
-                        const double* inv_s, double* out, hipStream_t s);
+// out = (A u) / s of the 3-D operator on node arrays, 0 on the ring; out must
+// not overlap u
+hipError_t launch_apply(const DeviceLevel& L, int nt, double dtheta, const double* u, const double* inv_s,
+                        double* out, hipStream_t s);
 hipError_t launch_norm_final(const double* partial, int nb, int nt, double* out, hipStream_t s);
 // One colour of zebra line relaxation on u (lines along r when along_r, else
 // along z); `scratch` is a node array of the level whose interior it may overwrite.

@@ -1,6 +1,6 @@
-// Single sweeps over a level's rows for gfx950: the operator, the plane norms,
-// the refinement step of the mixed-precision solve, and the restriction of the
-// finest right-hand side.
+// Single sweeps over a level's rows for gfx950: the plane norms, the refinement
+// step of the mixed-precision solve, and the restriction of the finest
+// right-hand side.
 //
 // One wavefront owns a strip of column pairs of one plane (62 pairs, one more
 // lane on either side for the neighbours' values) and a chunk of rows, and
@@ -50,7 +50,6 @@ struct RowArgs {
     const double* u;
     const double* f;
     const float* e;
-    const double* inv_s;
     double* out;
     float* r32;
     double* partial;   // [plane][kMaxPartial]: sums of r^2 ...
@@ -95,31 +94,28 @@ __device__ __forceinline__ double wave_sum(double x) {
     return x;
 }
 
-// What a sweep evaluates.  kApply: out = (A u) / s on the interior and zero on
-// the ring.  kNormX: sums of f^2.  kNormR, kNormB, kNormBoth: sums of squares of the residual
+// What a sweep evaluates.  kNormX: sums of f^2.  kNormR, kNormB, kNormBoth: sums of squares of the residual
 // r = f - A u, of the right-hand side b (the residual of u's ring around a
 // zero interior), or both.  kRefineZero, kRefineAsIs, kRefineAdd: sums of r^2
 // and r rounded to FP32 for the iterate u's ring around a zero interior, u, or
 // u + e (e zero on the ring), which the first and last also store into out.
-enum RowMode { kApply, kNormX, kNormR, kNormB, kNormBoth, kRefineZero, kRefineAsIs, kRefineAdd };
+enum RowMode { kNormX, kNormR, kNormB, kNormBoth, kRefineZero, kRefineAsIs, kRefineAdd };
 
-// Measured: kApply at 257 x 128 x 257 moves 135 MB in 33 us (54 us as one
-// thread a node, whose vertical neighbours came back from cache), kRefineAdd at
-// 257 x 64 x 257 136 MB in 28.6 us and kRefineZero 85 MB in 18.7 us (34 and 29
-// as workgroups of a row's columns sharing rows through LDS, a barrier a row).
-// At 129 x 64 x 129, where launches count, kNormBoth and its sums take 9 + 3 us
-// for what were a residual written and read again and three sums (37 us).
+// Measured: kRefineAdd at 257 x 64 x 257 moves 136 MB in 28.6 us and
+// kRefineZero 85 MB in 18.7 us (34 and 29 as workgroups of a row's columns
+// sharing rows through LDS, a barrier a row).  At 129 x 64 x 129, where launches
+// count, kNormBoth and its sums take 9 + 3 us for what were a residual written
+// and read again and three sums (37 us).
 template <int MODE>
 __global__ void __launch_bounds__(64, 4) k_rows(RowArgs a) {
 #pragma clang fp contract(off)
     constexpr bool RING = MODE == kNormB || MODE == kRefineZero;  // reads u's ring only
-    constexpr bool F = MODE != kApply;
     constexpr bool U = MODE != kNormX;
-    constexpr bool R = U && F && MODE != kNormB;
+    constexpr bool R = U && MODE != kNormB;
     constexpr bool B = MODE == kNormB || MODE == kNormBoth;
     constexpr bool REFINE = MODE == kRefineZero || MODE == kRefineAsIs || MODE == kRefineAdd;
     constexpr bool ADD = MODE == kRefineAdd;
-    constexpr bool OUT = MODE == kApply || MODE == kRefineZero || ADD;
+    constexpr bool OUT = MODE == kRefineZero || ADD;
     const LevelView& v = a.v;
     Strip w;
     w.place(a.sh, v);
@@ -129,13 +125,12 @@ __global__ void __launch_bounds__(64, 4) k_rows(RowArgs a) {
     // buffers from the row before the chunk on; rows are offsets from it
     const long long first = (long long)w.p * v.pstride + (long long)s * v.pitch;
     const long long left = (long long)(v.nz - s) * v.pitch;
-    rsrc_t ru, rf, re, ro, r3, ri;
+    rsrc_t ru, re, ro, r3;
     if (U) ru = make_rsrc(a.u + first, left);
-    if (F) rf = make_rsrc(a.f + first, left);
+    const rsrc_t rf = make_rsrc(a.f + first, left);
     if (ADD) re = make_rsrc(a.e + first, left);
     if (OUT) ro = make_rsrc(a.out + first, left);
     if (REFINE) r3 = make_rsrc(a.r32 + first, left);
-    if (MODE == kApply) ri = make_rsrc(a.inv_s + (long long)s * v.pitch, left);
     const unsigned row8 = (unsigned)(v.pitch * 8), row4 = (unsigned)(v.pitch * 4);
     double acc = 0.0, accb = 0.0;
     for (int strip = w.strip0; strip < a.sh.nstrips; strip += a.sh.bs) {
@@ -146,8 +141,6 @@ __global__ void __launch_bounds__(64, 4) k_rows(RowArgs a) {
         const unsigned vring = a0 && a1 ? kOff : voff;
         const unsigned vin = any ? voff : kOff, vin4 = any ? (unsigned)c1 * 4 : kOff;
         const unsigned vst = w.own ? vin : kOff, vst4 = w.own ? vin4 : kOff;
-        // the ring column of an odd count of columns has no partner
-        const unsigned vlast = w.own && c1 == v.nr - 1 ? voff : kOff;
         auto load_u = [&](int x) -> Pair<double> {
             if (!U) return {0.0, 0.0};
             const int xr = min(x, zb);
@@ -172,7 +165,7 @@ __global__ void __launch_bounds__(64, 4) k_rows(RowArgs a) {
                 if (in && a1) o[1] = l.b + (double)d.b;
             }
         };
-        Pair<double> pu[kAhead], pf[kAhead], pi[kAhead];
+        Pair<double> pu[kAhead], pf[kAhead];
         Pair<float> pe[kAhead];
         double lo[2], mid[2], hi[2];
         {
@@ -186,38 +179,26 @@ __global__ void __launch_bounds__(64, 4) k_rows(RowArgs a) {
             for (int j = 0; j < kAhead; ++j) {
                 pu[j] = load_u(za + 1 + j);
                 if (ADD) pe[j] = load_e(za + 1 + j);
-                if (F) pf[j] = load_f(za + j);
-                if (MODE == kApply) pi[j] = load2<double>(ri, vin, (unsigned)(min(za + j, zb) - s) * row8);
+                pf[j] = load_f(za + j);
             }
             value(s, l0, e0, lo);
             value(za, l1, e1, mid);
-        }
-        if (MODE == kApply && za == 1) {
-            store2<double>(ro, c1 + 1 < v.nr && w.own ? voff : kOff, 0, 0.0, 0.0);
-            store1<double>(ro, vlast, 0, 0.0);
         }
         for (int x0 = za; x0 < zb; x0 += kAhead) {
 #pragma unroll
             for (int j = 0; j < kAhead; ++j) {
                 const int x = x0 + j;
                 value(x + 1, pu[j], pe[j], hi);
-                const Pair<double> f = pf[j], is = pi[j];
+                const Pair<double> f = pf[j];
                 pu[j] = load_u(x + 1 + kAhead);
                 if (ADD) pe[j] = load_e(x + 1 + kAhead);
-                if (F) pf[j] = load_f(x + kAhead);
-                if (MODE == kApply) pi[j] = load2<double>(ri, vin, (unsigned)(min(x + kAhead, zb) - s) * row8);
+                pf[j] = load_f(x + kAhead);
                 if (x < zb) {
                     const double zc = zct[x], zs = zst[x], zn = znt[x];
                     const Coef k0 = make_coef_products(w.rw[0], w.re[0], w.rb[0], w.rm[0], zc, zs, zn, lam);
                     const Coef k1 = make_coef_products(w.rw[1], w.re[1], w.rb[1], w.rm[1], zc, zs, zn, lam);
                     const double west = from_lane<true>(mid[1]), east = from_lane<false>(mid[0]);
                     const unsigned so = (unsigned)(x - s) * row8;
-                    if (MODE == kApply) {
-                        const double o0 = apply_row(mid[0], west, mid[1], lo[0], hi[0], k0) * is.a;
-                        const double o1 = apply_row(mid[1], mid[0], east, lo[1], hi[1], k1) * is.b;
-                        store2<double>(ro, vst, so, a0 ? o0 : 0.0, a1 ? o1 : 0.0);
-                        store1<double>(ro, vlast, so, 0.0);
-                    }
                     if (R) {
                         const double r0 = residual(mid[0], f.a, west, mid[1], lo[0], hi[0], k0);
                         const double r1 = residual(mid[1], f.b, mid[0], east, lo[1], hi[1], k1);
@@ -250,11 +231,6 @@ __global__ void __launch_bounds__(64, 4) k_rows(RowArgs a) {
                     mid[c] = hi[c];
                 }
             }
-        }
-        if (MODE == kApply && zb == v.nz - 1) {
-            const unsigned so = (unsigned)(zb - s) * row8;
-            store2<double>(ro, c1 + 1 < v.nr && w.own ? voff : kOff, so, 0.0, 0.0);
-            store1<double>(ro, vlast, so, 0.0);
         }
     }
     if (R || MODE == kNormX) {
@@ -419,6 +395,7 @@ __global__ void __launch_bounds__(64) k_norm_final(const double* __restrict__ pa
 
 template <int MODE>
 hipError_t launch_rows(RowArgs& a, int nt, hipStream_t s) {
+    if ((a.sh.chunk + 2LL) * a.v.pitch * 8 > kMaxRange) return hipErrorInvalidValue;
     k_rows<MODE><<<dim3(a.sh.nb, nt), 64, 0, s>>>(a);
     return hipGetLastError();
 }
@@ -436,15 +413,6 @@ RowArgs row_args(const DeviceLevel& L, int nt, const double* lam, int most) {
 hipError_t launch_norm_final(const double* partial, int nb, int nt, double* out, hipStream_t s) {
     k_norm_final<<<nt, 64, 0, s>>>(partial, nb, 0, out, nullptr);
     return hipGetLastError();
-}
-
-hipError_t launch_apply(const DeviceLevel& L, int nt, const double* lam, const double* u,
-                        const double* inv_s, double* out, hipStream_t s) {
-    RowArgs a = row_args(L, nt, lam, 1 << 20);
-    a.u = u;
-    a.inv_s = inv_s;
-    a.out = out;
-    return launch_rows<kApply>(a, nt, s);
 }
 
 hipError_t launch_plane_norms(const DeviceLevel& L, int nt, const double* x, double* partial,

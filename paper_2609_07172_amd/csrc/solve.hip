@@ -1423,11 +1423,13 @@ int cylpoisson_apply(cylpoisson_plan* p, const double* phi, double* rho_out, voi
     if (st == CYLPOISSON_OK) st = check_device_range(p, rho_out, bytes, "rho_out");
     if (st != CYLPOISSON_OK) return st;
     hipStream_t s = static_cast<hipStream_t>(stream);
-    DeviceLevel& L = p->dl[0];
-    // every solve writes all of f before it reads any
-    CP_HIP(transform(p, false, phi, L.f, nullptr, s));
-    CP_HIP(launch_apply(L, p->nt, p->d_lam, L.f, p->d_inv_s, p->d_tmp, s));
-    CP_HIP(transform(p, true, p->d_tmp, rho_out, nullptr, s));
+    const char* a = (const char*)phi;
+    const char* b = (const char*)rho_out;
+    if (a < b + bytes && b < a + bytes) {  // in place: from a copy
+        CP_HIP(hipMemcpyAsync(p->d_tmp, phi, bytes, hipMemcpyDeviceToDevice, s));
+        phi = p->d_tmp;
+    }
+    CP_HIP(launch_apply(p->dl[0], p->nt, p->dtheta, phi, p->d_inv_s, rho_out, s));
     return CYLPOISSON_OK;
 }
 
