@@ -313,9 +313,9 @@ int cylpoisson_autotune(cylpoisson_plan* plan, void* stream);
 
 /* Solve `count` independent problems (distinct plans, each with its own grid)
  * together: problem i solves plans[i] with rho[i] -> phi[i] exactly as
- * cylpoisson_solve would, all problems running concurrently on streams of
- * their own (ordered after the work already on `stream`; `stream` waits for
- * all of them on return), so small problems fill the GPU together.  The same
+ * cylpoisson_solve would, a few problems at a time on streams of the
+ * library's, the largest first (ordered after the work already on `stream`,
+ * and complete on return), so small problems fill the GPU together.  The same
  * tol for all; statuses (optional, count entries) receives each problem's
  * status, and each plan's stats hold its own history.  Returns the first
  * negative status, else NOT_CONVERGED if any problem did not converge, else

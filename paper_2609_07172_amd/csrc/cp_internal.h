@@ -188,6 +188,7 @@ struct cylpoisson_plan {
     double* d_r0 = nullptr;  // level-0 radii (nr), for the learned preconditioner's input
     // the kernels read d_mask only while a masked V-cycle iteration keeps it
     // current (set for the duration of run_cycles with masks active)
+    int share = 1;               // solves that run beside this plan's (a batch), itself included
     bool mask_live = false;
     cp::Options opt;
     // cycles and tol of the last solve that converged (0: none since the
@@ -237,6 +238,7 @@ struct cylpoisson_plan {
     // plane groups: one extra stream per group after the first, and events to
     // fork from / join into the caller's stream (created on first use)
     std::vector<hipStream_t> gstreams;
+    std::vector<hipStream_t> lanes;  // streams of the batches this plan leads
     std::vector<hipEvent_t> gevents;
 
     // per-plane convergence masks (1 = active), device and pinned host copies

@@ -679,7 +679,7 @@ Shape pass_shape(const cylpoisson_plan* p, int l, int nu, bool down, bool merge 
     const bool automatic = chunk <= 0;
     if (automatic) {
         // as many chunks as keep every wavefront resident at once
-        const int per_plane = std::max(1, kPassWaves * pass_waves(nu, sh.coef) / 2 / (p->nt * sh.nstrips));
+        const int per_plane = std::max(1, kPassWaves * pass_waves(nu, sh.coef) / 2 / (p->share * p->nt * sh.nstrips));
         chunk = std::max(kMinChunk, (rows + per_plane - 1) / per_plane);
     }
     // an up pass keeps one norm partial per wavefront: at most 64 a plane

@@ -230,6 +230,8 @@ void free_plan(cylpoisson_plan* p) {
     p->gevents.clear();
     for (hipStream_t st : p->gstreams) (void)hipStreamDestroy(st);
     p->gstreams.clear();
+    for (hipStream_t st : p->lanes) (void)hipStreamDestroy(st);
+    p->lanes.clear();
     drop_graphs(p);
     if (p->cap_stream) (void)hipStreamDestroy(p->cap_stream);
     p->cap_stream = nullptr;
