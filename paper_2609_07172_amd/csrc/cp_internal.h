@@ -401,6 +401,8 @@ void direct_tables(const HostLevel& H, std::vector<double>& V, std::vector<doubl
 void direct_pack(const HostLevel& H, bool big, const std::vector<double>& V, const std::vector<double>& sigma,
                  const std::vector<double>& lam, int nc, std::vector<double>& Vp, std::vector<double>& VTp,
                  std::vector<double>& M);
+// group size of the one-workgroup form: 16 G interior nodes each way
+int direct_g(const HostLevel& H);
 // the level the option "direct" selects (-1 when off or none)
 int direct_level(const cylpoisson_plan* p);
 bool direct_active(const cylpoisson_plan* p);
@@ -452,6 +454,12 @@ void drop_graphs(cylpoisson_plan* p);
 // Every level above the bottom kernel has fused passes (plan.hip).
 bool mixed_supported(const cylpoisson_plan* p);
 hipError_t fused_up32(cylpoisson_plan* p, int l, hipStream_t s, int p0 = 0, int np = -1);
+// every cycle between two checks of small planes in one launch (plane.hip);
+// u holds the start (see run_segment) and the answer, the last cycle's norms go
+// to partial, one sum a plane
+bool plane_active(const cylpoisson_plan* p);
+hipError_t launch_plane(cylpoisson_plan* p, int cycles, bool zero_top, bool pro, double* partial, int partial_ld,
+                        hipStream_t s);
 // the finest level's merged pass in FP32 (two sweeps of either kind): up pass
 // and prolongation of one inner cycle, down pass of the next (all planes)
 bool fused_merge32_ok(const cylpoisson_plan* p);

@@ -420,11 +420,22 @@ void reset_stats(cylpoisson_plan* p) {
 // Options that change launch parameters drop the cache.
 bool graphs_active(const cylpoisson_plan* p, int G) { return p->opt.graph && G == 1 && !p->opt.timing; }
 
+// Cycles c0 .. ce of small planes in one launch; the host sees them as merged
+// cycles and an up pass with one partial sum a plane.
+hipError_t plane_segment(cylpoisson_plan* p, hipStream_t s, int c0, int ce, bool zero_top, bool pro,
+                         std::vector<NormSlot>& slots) {
+    for (int c = c0; c < ce; ++c) slots[c].partial_chunks = kNoNorms;
+    slots[ce].partial_chunks = 1;
+    return launch_plane(p, ce - c0 + 1, zero_top, pro, p->d_slot_partial + (size_t)ce * p->nt * kSlotPartial,
+                        kSlotPartial, s);
+}
+
 // Cycles c0 .. ce as the eager loop runs them, the last one ending in the up
 // pass whose norms the check reads; the cycles before it end in the merged
 // finest pass when `merging`.
 hipError_t run_segment(cylpoisson_plan* p, hipStream_t s, int c0, int ce, bool zero_top, bool pro, bool merging,
                        std::vector<NormSlot>& slots) {
+    if (merging && plane_active(p)) return plane_segment(p, s, c0, ce, zero_top, pro, slots);
     bool pending = false;
     hipError_t e = hipSuccess;
     for (int c = c0; c <= ce && e == hipSuccess; ++c) {
@@ -454,7 +465,7 @@ hipError_t run_segment(cylpoisson_plan* p, hipStream_t s, int c0, int ce, bool z
 hipError_t graph_segment(cylpoisson_plan* p, hipStream_t s, int c0, int ce, bool zero_top, bool pro, bool merging,
                          std::vector<NormSlot>& slots) {
     const int flags = (zero_top ? 1 : 0) | (pro ? 2 : 0) | (merging ? 4 : 0);
-    const int merges = merging ? ce - c0 : 0;
+    const int merges = merging && !plane_active(p) ? ce - c0 : 0;
     for (const GraphSeg& g : p->graphs)
         if (g.c0 == c0 && g.ce == ce && g.flags == flags && g.u == p->dl[0].u) {
             for (int c = c0; c <= ce; ++c) slots[c].partial_chunks = g.chunks[c - c0];
@@ -798,6 +809,10 @@ int run_cycles(cylpoisson_plan* p, double tol, hipStream_t s, bool ring_only, bo
             // every cycle up to the next check in one replay
             const int ce = std::min(std::max(next_check, c), maxc);
             CP_HIP(graph_segment(p, s, c, ce, c == 1 && ring_only, c == 1 && fmg_pro, merge_ok, slots));
+            c = ce;
+        } else if (merging && plane_active(p)) {
+            const int ce = std::min(std::max(next_check, c), maxc);
+            CP_HIP(plane_segment(p, s, c, ce, c == 1 && ring_only, c == 1 && fmg_pro, slots));
             c = ce;
         } else if (merging) {
             if (!pending) CP_HIP(cycle_down(p, s, c == 1 && ring_only, c == 1 && fmg_pro));
