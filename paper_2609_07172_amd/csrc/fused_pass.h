@@ -119,6 +119,7 @@ constexpr int strip_step(int nu) { return 62 - 2 * nu; }
 
 constexpr int kPassWaves = 2048;  // wavefronts of an automatic launch shape at two per SIMD
 constexpr int kMinChunk = 4;      // rows per chunk at least
+constexpr int kShortChunk = 20;   // rows of a merged chunk up to which one wavefront a SIMD is enough
 constexpr int kFewRows = 4;       // rows outside the band that kSomeRows serves: two next to each face
 
 // ---- buffer access: a scalar base and range, 32-bit lane and row offsets ----
@@ -679,8 +680,20 @@ Shape pass_shape(const cylpoisson_plan* p, int l, int nu, bool down, bool merge 
     const bool automatic = chunk <= 0;
     if (automatic) {
         // as many chunks as keep every wavefront resident at once
-        const int per_plane = std::max(1, kPassWaves * pass_waves(nu, sh.coef) / 2 / (p->share * p->nt * sh.nstrips));
-        chunk = std::max(kMinChunk, (rows + per_plane - 1) / per_plane);
+        auto rows_for = [&](int waves) {
+            const int per_plane = std::max(1, waves / (p->share * p->nt * sh.nstrips));
+            return std::max(kMinChunk, (rows + per_plane - 1) / per_plane);
+        };
+        chunk = rows_for(kPassWaves * pass_waves(nu, sh.coef) / 2);
+        // A merged chunk of c rows runs c + 19 or so steps.  Where it is short, a
+        // second wavefront a SIMD mostly repeats rows of the first: up to
+        // kShortChunk rows with one, one it is (151 x 45 x 203, 10 rows or 19: 382
+        // and 366 us the solve; 129 x 64 x 129, 8 or 16: 275 and 268; 101 x 64 x 401,
+        // 13 or 25: 549 and 546; 400 x 128 x 512, 128 or 255: 2412 and 2522).
+        if (merge && p->share == 1 && pass_waves(nu, sh.coef) == 2) {
+            const int longer = rows_for(kPassWaves / 2);
+            if (longer <= kShortChunk) chunk = longer;
+        }
     }
     // an up pass keeps one norm partial per wavefront: at most 64 a plane
     // (what a check reads back) unless the caller asked for more chunks than
