@@ -430,7 +430,7 @@ def time_batch(args, batch):
     out = {"problems": [q.name for q in probs], "unknowns": unknowns, "tol": args.tol, "options": {"fmg": 1},
            "rho": "manufactured phi_true(12345 + i)" if batch is not None else "blob",
            "batch_ms": round(batch_ms, 3), "sequential_ms": round(seq_ms, 3),
-           "launches": "one stream and host thread per problem", "statuses": sts,
+           "launches": "up to three lanes, each a stream and a host thread, largest problem first", "statuses": sts,
            "cycles": [s["cycles"] for s in stats], "worst_rel_residual": max(s["rel_residual"] for s in stats)}
     if batch is not None:
         out["rel_l2_vs_oracle"] = [interior_rel(g, b[1]) for g, b in zip(got, batch)]
