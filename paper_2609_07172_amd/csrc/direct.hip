@@ -83,13 +83,20 @@ __global__ void __launch_bounds__(64 * G * G) k_direct(DirectArgs<T> a) {
     const int grp = wave / G, col = 16 * (wave % G) + cl;
     const size_t base = (size_t)plane * v.pstride + v.pitch + 1;  // interior (0, 0)
     const bool in = col < nri;
+    T fv[KS];
     double fb[KS], va[KS];
 #pragma unroll
     for (int s = 0; s < KS; ++s) {
         const int k = 4 * s + kr;
-        fb[s] = in && k < nzi ? (double)a.f[base + (size_t)k * v.pitch + col] : 0.0;
+        // (FP32: no condition, see product())
+        if constexpr (sizeof(T) == 8)
+            fv[s] = in && k < nzi ? a.f[base + (size_t)k * v.pitch + col] : T(0);
+        else
+            fv[s] = a.f[base + (size_t)min(k, nzi - 1) * v.pitch + min(col, nri - 1)];
         va[s] = a.V[((size_t)grp * KS + s) * 64 + l];
     }
+#pragma unroll
+    for (int s = 0; s < KS; ++s) fb[s] = sizeof(T) == 8 || (in && 4 * s + kr < nzi) ? (double)fv[s] : 0.0;
     const int chain = t / NSEG, seg = t % NSEG;
     SegTables tb;
     tb.load(v, a.M + ((size_t)mode_of(plane, a.nc) * G + chain / 16) * (kSegRows * 16 * NSEG) + t % (16 * NSEG),
@@ -149,20 +156,30 @@ __device__ __forceinline__ bool big_block(int groups, int np, int* plane, int* g
 // workgroup calls it; wavefronts past the last column tile (!on) only stage.
 template <int KS, typename S>
 __device__ __forceinline__ void product(const double* __restrict__ A, int ks, int groups, int g0, double* as,
-                                        const S* __restrict__ src, size_t pitch, int n, int col, bool on, bool in,
+                                        const S* __restrict__ src, size_t pitch, int n, int col, int cols, bool on,
                                         int l, dbl4 (&acc)[kBigE]) {
     constexpr int NA = (kBigE * KS * 32 + kBigThreads - 1) / kBigThreads;  // 16-byte pieces per thread
     const double2* ag = reinterpret_cast<const double2*>(A + (size_t)g0 * ks * 64);
-    double fb[KS];
+    S fv[KS];
     double2 st[NA];
     // pieces past the last group's repeat its last one
     const int pieces = min(kBigE, groups - g0) * ks * 32;
 #pragma unroll
     for (int i = 0; i < NA; ++i) st[i] = ag[min((int)threadIdx.x + i * kBigThreads, pieces - 1)];
+    if constexpr (sizeof(S) == 8) {
 #pragma unroll
-    for (int s = 0; s < KS; ++s) {
-        const int k = 4 * s + (l >> 4);
-        fb[s] = in && k < n ? (double)src[(size_t)k * pitch + col] : 0.0;
+        for (int s = 0; s < KS; ++s) {
+            const int k = 4 * s + (l >> 4);
+            fv[s] = col < cols && k < n ? src[(size_t)k * pitch + col] : S(0);
+        }
+    } else if (on) {
+        // A load under a condition, converted, waits for itself (64 planes of
+        // 127 x 127: 21.6 us the forward kernel, 14.5 so), so rows and columns past
+        // the last repeat it and are dropped below.  In FP64, without the
+        // conversion, this costs the inverse kernel 1 us of its 20.5.
+        const S* at = src + min(col, cols - 1);
+#pragma unroll
+        for (int s = 0; s < KS; ++s) fv[s] = at[(size_t)min(4 * s + (l >> 4), n - 1) * pitch];
     }
 #pragma unroll
     for (int i = 0; i < NA; ++i)
@@ -171,6 +188,10 @@ __device__ __forceinline__ void product(const double* __restrict__ A, int ks, in
 #pragma unroll
     for (int e = 0; e < kBigE; ++e) acc[e] = dbl4{0.0, 0.0, 0.0, 0.0};
     if (!on) return;
+    double fb[KS];
+#pragma unroll
+    for (int s = 0; s < KS; ++s)
+        fb[s] = sizeof(S) == 8 || (col < cols && 4 * s + (l >> 4) < n) ? (double)fv[s] : 0.0;
     // (a group past the last multiplies the staging of the one before it or
     // what the LDS held: its results are not used)
 #pragma unroll
@@ -201,7 +222,7 @@ __global__ void __launch_bounds__(kBigThreads, 4) k_direct_fwd(DirectArgs<T> a) 
     {
         dbl4 acc[kBigE];
         product<KS>(a.V, a.ks, groups, g0, as, a.f + (size_t)plane * v.pstride + v.pitch + 1, v.pitch, nzi, col,
-                    16 * wave < nri, col < nri, l, acc);
+                    nri, 16 * wave < nri, l, acc);
         if (16 * wave < nri)
 #pragma unroll
             for (int e = 0; e < kBigE; ++e)
@@ -248,7 +269,7 @@ __global__ void __launch_bounds__(kBigThreads, 4) k_direct_inv(DirectArgs<T> a) 
     const int col = 16 * wave + (l & 15);
     dbl4 acc[kBigE];
     product<KS>(a.VT, a.ks, groups, g0, as, a.w + (size_t)plane * v.pstride + v.pitch + 1, v.pitch, nzi, col,
-                16 * wave < nri, col < nri, l, acc);
+                nri, 16 * wave < nri, l, acc);
     if (col >= nri) return;
     T* u = a.u + (size_t)plane * v.pstride + v.pitch + 1;
 #pragma unroll

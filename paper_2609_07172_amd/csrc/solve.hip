@@ -283,9 +283,9 @@ hipError_t vcycle(cylpoisson_plan* p, int l, hipStream_t s, bool zero_top, int s
 // passes on every level above the one where the V-cycle stops, the exact
 // solve's (in FP64) or the bottom kernel's.  Level 0 starts from a zero
 // correction when `zero_top`; coarser levels always do.
-// At 257 x 64 x 257 the exact solve of level 1 takes 33 us where the passes of
+// At 257 x 64 x 257 the exact solve of level 1 takes 26 us where the passes of
 // level 1 and the bottom kernel below it took 63, and four refinements reach
-// what took five (1290 us the solve, 804 now; 761 with the merged inner cycles).
+// what took five (1290 us the solve; 712 with that and the merged inner cycles).
 hipError_t vcycle32(cylpoisson_plan* p, int l, bool zero_top, hipStream_t s, int p0 = 0, int np = -1) {
     if (l > 0 && l == direct_level(p)) return launch_direct32(p, s, p0, np);
     if (l == p->bottom_level) return launch_bottom32(p, s, p0, np);
