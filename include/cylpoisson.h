@@ -184,7 +184,9 @@ void cylpoisson_plan_destroy(cylpoisson_plan* plan);
  *                    two rows ahead of the one they consume (1 .. 3; default 1)
  *   "timing"         1 = record per-kernel-class device times (cylpoisson_stats);
  *                    2 = the finest-level pass classes only (fewer event records
- *                    between the other launches); 0 = off (0 .. 2; default 0)
+ *                    between the other launches); 0 = off (0 .. 2; default 0).
+ *                    The cycles of small planes, otherwise one launch between two
+ *                    checks, run pass by pass when it is set (the same results)
  *   "bottom"         1 = run the small levels of each plane in one LDS-resident
  *                    kernel (with "fused" = 1; default 1)
  *   "smoother"       0 = point red-black SOR (default); 1 = zebra line relaxation

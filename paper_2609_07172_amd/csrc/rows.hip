@@ -23,6 +23,7 @@ constexpr int kStripPairs = 62;
 struct RowShape {
     int chunk, nchunks, nstrips;  // rows per chunk; chunks and strips per plane
     int nb;                       // wavefronts per plane
+    bool ok;                      // within the partial sums and the 32-bit offsets
     int bs;                       // of them side by side (a wavefront takes every bs-th strip)
 };
 
@@ -40,6 +41,7 @@ RowShape row_shape(int rows, int nr, long long pitch, int nt, int most) {
     s.chunk = (int)std::max(1LL, std::min<long long>(s.chunk, kMaxRange / (pitch * 8) - 2 * kAhead));
     s.nchunks = (rows + s.chunk - 1) / s.chunk;
     s.nb = s.nchunks * s.bs;
+    s.ok = s.nb <= most && (s.chunk + 2LL) * pitch * 8 <= kMaxRange;
     return s;
 }
 
@@ -395,7 +397,7 @@ __global__ void __launch_bounds__(64) k_norm_final(const double* __restrict__ pa
 
 template <int MODE>
 hipError_t launch_rows(RowArgs& a, int nt, hipStream_t s) {
-    if ((a.sh.chunk + 2LL) * a.v.pitch * 8 > kMaxRange) return hipErrorInvalidValue;
+    if (!a.sh.ok) return hipErrorInvalidValue;
     k_rows<MODE><<<dim3(a.sh.nb, nt), 64, 0, s>>>(a);
     return hipGetLastError();
 }
@@ -457,6 +459,7 @@ hipError_t launch_restrict_rhs_norms(const DeviceLevel& F, const DeviceLevel& C,
     a.fc = fc;
     a.partial = partial;
     a.rc = C.v.nr < F.v.nr;
+    if (!a.sh.ok) return hipErrorInvalidValue;
     const dim3 grid(a.sh.nb, nt);
     if (zc)
         k_restrict_rhs<true><<<grid, 64, 0, s>>>(a);
