@@ -225,10 +225,12 @@ struct Stream {
         for (int kb = 0; kb < 3; ++kb) {
             w1[kb] = operand(w0p, kb, lane);
             // block kb of the first layer holds taps 4 kb + g (four channels
-            // each); past the ninth tap the weights are zero
+            // each); past the ninth tap the weights are zero and the operand is
+            // the zero before the row's first pixel (a pixel's own value may be
+            // infinite)
             const int tap = min(4 * kb + g, 8);
             in_dy[kb] = tap / 3 - 1;
-            in_off[kb] = (px + 1 + tap % 3 - 1) * 4;
+            in_off[kb] = 4 * kb + g <= 8 ? (px + 1 + tap % 3 - 1) * 4 : 0;
         }
 #pragma unroll
         for (int tap = 0; tap < 9; ++tap) w2[tap] = operand(w1p, tap, lane);

@@ -1,0 +1,56 @@
+"""Infinite values in the network: each one reaches exactly the results whose
+taps it belongs to.  Products with the zero weights and zero gradients that only
+pad an operand would turn it into NaN.
+
+Weights and inputs are positive, so that sums of infinities stay infinite; the
+finite entries' tolerances are those of the network's other tests (BF16 ties
+decided by FP32 rounding): 1e-4 on outputs, 5e-4 on gradients.
+"""
+import numpy as np
+import pytest
+import torch
+
+from gpu_util import say
+from oracle import nn
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def P():
+    import paper_2609_07172_amd as P
+
+    P.library()
+    return P
+
+
+def positive_net(P):
+    rng = np.random.Generator(np.random.PCG64(3))
+    params = [rng.uniform(0.01, 0.1, (9, ci, co)).astype(np.float32) for ci, co in nn.SHAPES]
+    net = P.Net(seed=1)
+    net.set_weights(np.concatenate([w.ravel() for w in params]))
+    return net, [w.astype(np.float64) for w in params], rng
+
+
+def same(got, ref, tol):
+    got, ref = np.asarray(got, dtype=np.float64), np.asarray(ref, dtype=np.float64)
+    assert (np.isnan(got) == np.isnan(ref)).all(), (np.isnan(got).sum(), np.isnan(ref).sum())
+    assert (got[np.isinf(ref)] == ref[np.isinf(ref)]).all()
+    ok = np.isfinite(ref)
+    assert np.isfinite(got[ok]).all()
+    assert np.linalg.norm(got[ok] - ref[ok]) <= tol * np.linalg.norm(ref[ok])
+
+
+# one strip of each width, and two strips with the value on either side of their border
+@pytest.mark.parametrize("shape", [(9, 26), (9, 42), (9, 58), (20, 70)], ids=lambda s: "x".join(map(str, s)))
+def test_forward(P, shape):
+    H, W = shape
+    say("infinite input", shape)
+    net, params, rng = positive_net(P)
+    where = [(0, 0), (H - 1, W - 1), (4, 5), (H // 2, W // 2), (5, min(W - 1, 57)), (6, min(W - 1, 58))]
+    x = rng.uniform(0.1, 1.0, (len(where), H, W, 4)).astype(np.float32)
+    for b, (i, j) in enumerate(where):
+        x[b, i, j, b % 4] = np.inf
+    ref, _ = nn.forward(params, x.astype(np.float64))
+    assert np.isinf(ref).any() and not np.isnan(ref).any()
+    same(net.forward(torch.from_numpy(x).to("cuda:0")).cpu().numpy(), ref, 1e-4)
