@@ -424,10 +424,12 @@ __global__ void __launch_bounds__(kBThreads) k_net_bwd(const float* __restrict__
                 v4s bv;
 #pragma unroll
                 for (int h = 0; h < 2; ++h) {
-                    const int tap = min(kb * 8 + 2 * g + h, 8);  // past the ninth tap the weights are zero
+                    // past the ninth tap the weights are zero, and so is the
+                    // operand (a gradient may be infinite)
+                    const int k = kb * 8 + 2 * g + h, tap = min(k, 8);
                     const short* s = G3 + ((pr + 1 - (tap / 3 - 1)) * (kBW + 4) + pc + 1 - (tap % 3 - 1)) * 2;
-                    bv[2 * h] = s[0];
-                    bv[2 * h + 1] = s[1];
+                    bv[2 * h] = k <= 8 ? s[0] : (short)0;
+                    bv[2 * h + 1] = k <= 8 ? s[1] : (short)0;
                 }
                 acc = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(w2[kb], bv, acc, 0, 0, 0);
             }

@@ -54,3 +54,52 @@ def test_forward(P, shape):
     ref, _ = nn.forward(params, x.astype(np.float64))
     assert np.isinf(ref).any() and not np.isnan(ref).any()
     same(net.forward(torch.from_numpy(x).to("cuda:0")).cpu().numpy(), ref, 1e-4)
+
+
+def weight_grad(x, g):
+    """nn.weight_grad with every product formed (a zero gradient under an infinite activation is NaN)."""
+    B, H, W, c = x.shape
+    xp = np.pad(x, ((0, 0), (1, 1), (1, 1), (0, 0)))
+    out = []
+    for dy, dx in nn.TAPS:
+        xs = xp[:, 1 + dy:1 + dy + H, 1 + dx:1 + dx + W].reshape(-1, c, 1)
+        out.append((xs * g.reshape(-1, 1, g.shape[3])).sum(axis=0))
+    return np.array(out)
+
+
+def gradients(params, x, target):
+    """The oracle's gradients with those products."""
+    y, acts = nn.forward(params, x)
+    inner = nn.inner_mask(*y.shape[1:3])[None, :, :, None] > 0
+    g = np.where(inner, y - target, 0.0) / (y.shape[0] * inner.sum() * 2)
+    grads = [None] * 3
+    for l in (2, 1, 0):
+        g = nn.bf16(g)
+        grads[l] = weight_grad(acts[l], g)
+        if l:
+            g = np.where(acts[l] > 0.0, nn.conv_adjoint(g, nn.bf16(params[l])), 0.0)
+    return grads
+
+
+def check_gradients(P, x, target, net, params):
+    with np.errstate(invalid="ignore"):
+        ref = gradients(params, x.astype(np.float64), target.astype(np.float64))
+    net.loss_grad(torch.from_numpy(x).to("cuda:0"), torch.from_numpy(target).to("cuda:0"))
+    got, at = net.get_grads(), 0
+    for l, (ci, co) in enumerate(nn.SHAPES):
+        n = 9 * ci * co
+        same(got[at:at + n], ref[l].ravel(), 5e-4)
+        at += n
+    return ref
+
+
+def test_infinite_target(P):
+    """Every gradient through the one infinite pixel of the output is infinite, none is NaN."""
+    H, W = 16, 32
+    say("infinite target", (H, W))
+    net, params, rng = positive_net(P)
+    x = rng.uniform(0.1, 1.0, (2, H, W, 4)).astype(np.float32)
+    target = rng.uniform(0.1, 1.0, (2, H, W, 2)).astype(np.float32)
+    target[0, 8, 11, 1] = np.inf
+    ref = check_gradients(P, x, target, net, params)
+    assert np.isinf(ref[0]).all() and np.isinf(ref[1]).all()
