@@ -467,6 +467,12 @@ __global__ void __launch_bounds__(kBThreads) k_net_bwd(const float* __restrict__
 #pragma unroll 1
         for (int blk = wave; blk < kBH * kBW / 16; blk += kBWaves) {
             const int pr = blk / (kBW / 16), pc = (blk % (kBW / 16)) * 16 + 4 * g;
+            // a pixel outside the image has a zero gradient and must have a zero
+            // activation too: the one beside it may be infinite
+            if (y0 + pr >= H) continue;
+            v4s in;  // all ones for those of the lane's four pixels in the image
+#pragma unroll
+            for (int j = 0; j < 4; ++j) in[j] = x0 + pc + j < W ? (short)-1 : (short)0;
             v4s b1, b2, b3;
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
@@ -485,8 +491,8 @@ __global__ void __launch_bounds__(kBThreads) k_net_bwd(const float* __restrict__
                 }
 #pragma unroll
                 for (int dx = 0; dx < 3; ++dx) {
-                    const v4s c1 = {e1[dx], e1[dx + 1], e1[dx + 2], e1[dx + 3]};
-                    const v4s c2 = {e2[dx], e2[dx + 1], e2[dx + 2], e2[dx + 3]};
+                    const v4s c1 = v4s{e1[dx], e1[dx + 1], e1[dx + 2], e1[dx + 3]} & in;
+                    const v4s c2 = v4s{e2[dx], e2[dx + 1], e2[dx + 2], e2[dx + 3]} & in;
                     acc2[3 * dy + dx] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(c1, b2, acc2[3 * dy + dx], 0, 0, 0);
                     acc3[3 * dy + dx] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(c2, b3, acc3[3 * dy + dx], 0, 0, 0);
                 }
@@ -500,6 +506,7 @@ __global__ void __launch_bounds__(kBThreads) k_net_bwd(const float* __restrict__
                     const short v = X[((pr + tap / 3) * (kBW + 2) + pc + tap % 3 + j) * 4 + (r & 3)];
                     c[j] = r < 36 ? v : (short)0;
                 }
+                c &= in;
                 acc1[m] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(c, b1, acc1[m], 0, 0, 0);
             }
         }

@@ -103,3 +103,19 @@ def test_infinite_target(P):
     target[0, 8, 11, 1] = np.inf
     ref = check_gradients(P, x, target, net, params)
     assert np.isinf(ref[0]).all() and np.isinf(ref[1]).all()
+
+
+# images that end inside a tile of 16 x 32 pixels, in the first tile and in the second
+@pytest.mark.parametrize("shape", [(13, 29), (20, 40)], ids=lambda s: "x".join(map(str, s)))
+@pytest.mark.parametrize("edge", ["corner", "row", "column"])
+def test_infinite_edge_activation(P, shape, edge):
+    """The weight gradients sum over the image's pixels: beside its last row and
+    column lie tile positions outside it, with zero gradients, which add nothing."""
+    H, W = shape
+    say("infinite edge", shape, edge)
+    net, params, rng = positive_net(P)
+    x = rng.uniform(0.1, 1.0, (2, H, W, 4)).astype(np.float32)
+    target = rng.uniform(0.1, 1.0, (2, H, W, 2)).astype(np.float32)
+    x[(0, *{"corner": (H - 1, W - 1), "row": (H - 1, 10), "column": (8, W - 1)}[edge], 1)] = np.inf
+    ref = check_gradients(P, x, target, net, params)
+    assert np.isinf(ref[0]).sum() == 528
