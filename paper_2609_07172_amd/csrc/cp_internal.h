@@ -152,6 +152,7 @@ constexpr int kDirectBigMax = 128;
 // chunks each cycle recorded.
 struct GraphSeg {
     int c0, ce, flags;
+    int share;  // launch shapes depend on the solves running beside (cylpoisson_plan::share)
     const double* u;
     hipGraphExec_t exec;
     std::vector<int> chunks;

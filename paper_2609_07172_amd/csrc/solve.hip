@@ -467,7 +467,7 @@ hipError_t graph_segment(cylpoisson_plan* p, hipStream_t s, int c0, int ce, bool
     const int flags = (zero_top ? 1 : 0) | (pro ? 2 : 0) | (merging ? 4 : 0);
     const int merges = merging && !plane_active(p) ? ce - c0 : 0;
     for (const GraphSeg& g : p->graphs)
-        if (g.c0 == c0 && g.ce == ce && g.flags == flags && g.u == p->dl[0].u) {
+        if (g.c0 == c0 && g.ce == ce && g.flags == flags && g.share == p->share && g.u == p->dl[0].u) {
             for (int c = c0; c <= ce; ++c) slots[c].partial_chunks = g.chunks[c - c0];
             // the host's view of the finest buffers follows the replayed merges
             for (int i = 0; i < merges; ++i) std::swap(p->dl[0].u, p->dl[0].u2);
@@ -476,7 +476,7 @@ hipError_t graph_segment(cylpoisson_plan* p, hipStream_t s, int c0, int ce, bool
     hipError_t e = hipSuccess;
     if (!p->cap_stream) e = hipStreamCreateWithFlags(&p->cap_stream, hipStreamNonBlocking);
     if (e != hipSuccess) return e;
-    GraphSeg g{c0, ce, flags, p->dl[0].u, nullptr, {}};
+    GraphSeg g{c0, ce, flags, p->share, p->dl[0].u, nullptr, {}};
     e = hipStreamBeginCapture(p->cap_stream, hipStreamCaptureModeThreadLocal);
     if (e != hipSuccess) return e;
     hipError_t ev = run_segment(p, p->cap_stream, c0, ce, zero_top, pro, merging, slots);
