@@ -24,7 +24,8 @@ constexpr int kLanes = 3;
 
 // A pass alone is cut into enough chunks to fill the GPU, at the price of rows
 // computed twice; beside others it is cut into half as many (six uneven
-// problems: 2.56 ms without, 2.37 with, 2.47 at a third or a quarter).
+// problems: 2.56 ms without, 2.37 with, 2.47 at a third or a quarter), but for
+// the pass that leaves the norms, whose sums stay those of a solve alone (2.40).
 constexpr int kShare = 2;
 
 // One device's problems, in the order they are taken, and its lanes' streams.

@@ -678,10 +678,13 @@ Shape pass_shape(const cylpoisson_plan* p, int l, int nu, bool down, bool merge 
     const int rows = L.v.nz - 2;
     int chunk = merge ? p->opt.chunk_rows_merge : l == 0 ? p->opt.chunk_rows : p->opt.chunk_rows_coarse;
     const bool automatic = chunk <= 0;
+    // beside other solves fewer; but the finest FP64 up pass leaves the norms'
+    // partial sums, whose order must be that of a solve alone
+    const int share = l == 0 && !down && sizeof(T) == 8 ? 1 : p->share;
     if (automatic) {
         // as many chunks as keep every wavefront resident at once
         auto rows_for = [&](int waves) {
-            const int per_plane = std::max(1, waves / (p->share * p->nt * sh.nstrips));
+            const int per_plane = std::max(1, waves / (share * p->nt * sh.nstrips));
             return std::max(kMinChunk, (rows + per_plane - 1) / per_plane);
         };
         chunk = rows_for(kPassWaves * pass_waves(nu, sh.coef) / 2);
@@ -690,7 +693,7 @@ Shape pass_shape(const cylpoisson_plan* p, int l, int nu, bool down, bool merge 
         // kShortChunk rows with one, one it is (151 x 45 x 203, 10 rows or 19: 382
         // and 366 us the solve; 129 x 64 x 129, 8 or 16: 275 and 268; 101 x 64 x 401,
         // 13 or 25: 549 and 546; 400 x 128 x 512, 128 or 255: 2412 and 2522).
-        if (merge && p->share == 1 && pass_waves(nu, sh.coef) == 2) {
+        if (merge && share == 1 && pass_waves(nu, sh.coef) == 2) {
             const int longer = rows_for(kPassWaves / 2);
             if (longer <= kShortChunk) chunk = longer;
         }

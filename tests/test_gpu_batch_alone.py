@@ -37,3 +37,19 @@ def test_captured_graphs_of_a_batch_stay_with_the_batch(P, merge):
             b, sb = p.solve(r, tol=1e-12)
             assert (host(b) == a).all()
             assert sb["history"] == sa["history"]
+
+
+@pytest.mark.parametrize("options", [{}, {"merge": 0}, {"fmg": 1}, {"precision": 32}, {"masks": 1}, {"nu1": 3, "nu2": 3}], ids=str)
+def test_a_batch_solves_as_alone(P, options):
+    """Each problem exactly as alone: iterates, residual norms, checks and cycles."""
+    probs = [W.SMALL.with_sizes(*s) for s in SHAPES]
+    say("batch as alone", SHAPES, options)
+    rhos = [dev(W.blob_charge(p, 7)) for p in probs]
+    alone = [P.Plan.for_problem(p, **options) for p in probs]
+    plans = [P.Plan.for_problem(p, **options) for p in probs]
+    for _ in range(2):
+        phis, sts = P.solve_plans(plans, rhos, tol=1e-12)
+        for f, r, phi, sb in zip(alone, rhos, phis, sts):
+            a, sa = f.solve(r, tol=1e-12)
+            assert (host(phi) == host(a)).all()
+            assert (sb["cycles"], sb["checks"], sb["history"]) == (sa["cycles"], sa["checks"], sa["history"])
