@@ -5,6 +5,7 @@
 #include <algorithm>
 #include <atomic>
 #include <cmath>
+#include <memory>
 #include <string>
 #include <system_error>
 #include <thread>
@@ -36,6 +37,7 @@ struct Queue {
     std::atomic<int> next{0};
     cylpoisson_plan* keeper = nullptr;
     int lanes = 0;
+    std::vector<int> taken[kLanes];  // the problems each lane took, written by that lane alone
 };
 
 hipError_t ensure_lanes(cylpoisson_plan* p, int lanes) {
@@ -66,22 +68,23 @@ int solve_lanes(cylpoisson_plan* const* plans, const double* const* rho, double*
         if (start) (void)hipEventDestroy(start);
         return CYLPOISSON_EHIP;
     }
-    std::vector<Queue*> queues;
+    std::vector<std::unique_ptr<Queue>> queues;
     for (int i = 0; i < count; ++i) {
         Queue* q = nullptr;
-        for (Queue* c : queues)
-            if (c->keeper->device == plans[i]->device) q = c;
+        for (const auto& c : queues)
+            if (c->keeper->device == plans[i]->device) q = c.get();
         if (!q) {
-            q = new Queue;
+            queues.push_back(std::make_unique<Queue>());
+            q = queues.back().get();
             q->keeper = plans[i];
-            queues.push_back(q);
         }
         q->order.push_back(i);
     }
     auto nodes = [&](int i) { return (long long)plans[i]->nr * plans[i]->nt * plans[i]->nz; };
-    for (Queue* q : queues) {
+    for (const auto& q : queues) {
         std::stable_sort(q->order.begin(), q->order.end(), [&](int a, int b) { return nodes(a) > nodes(b); });
         q->lanes = std::min(kLanes, (int)q->order.size());
+        for (int l = 0; l < q->lanes; ++l) q->taken[l].reserve(q->order.size());
         bool ok = ensure_lanes(q->keeper, q->lanes) == hipSuccess;
         for (int l = 0; l < q->lanes && ok; ++l) ok = hipStreamWaitEvent(q->keeper->lanes[l], start, 0) == hipSuccess;
         if (!ok && status == CYLPOISSON_OK) {
@@ -95,29 +98,39 @@ int solve_lanes(cylpoisson_plan* const* plans, const double* const* rho, double*
             hipStream_t st = q->keeper->lanes[l];
             for (int k; (k = q->next.fetch_add(1)) < (int)q->order.size();) {
                 const int i = q->order[k];
+                q->taken[l].push_back(i);
                 res[i] = cylpoisson_solve(plans[i], rho[i], phi[i], tol, st);
                 msg[i] = cylpoisson_last_error();
             }
-            // the answers' last transforms
-            if (hipStreamSynchronize(st) != hipSuccess)
-                for (int i : q->order) res[i] = CYLPOISSON_EHIP;
+            // the answers' last transforms; if they are lost, so are this lane's
+            // answers, and no other's
+            const hipError_t e = hipStreamSynchronize(st);
+            if (e == hipSuccess) return;
+            (void)hipGetLastError();
+            for (int i : q->taken[l])
+                if (res[i] >= 0) {
+                    res[i] = CYLPOISSON_EHIP;
+                    msg[i] = std::string("waiting for the answer: ") + hipGetErrorString(e);
+                }
         };
-        for (Queue* q : queues)
+        for (const auto& q : queues)
             for (int i : q->order) plans[i]->share = std::min(q->lanes, kShare);
         // the first lane of the first device runs on the caller's thread, and
         // so does one whose thread cannot be started
         std::vector<std::thread> threads;
         std::vector<std::pair<Queue*, int>> here;
-        for (Queue* q : queues)
+        threads.reserve(count);
+        here.reserve(count);
+        for (const auto& q : queues)
             for (int l = 0; l < q->lanes; ++l) {
                 if (q == queues[0] && l == 0) {
-                    here.emplace_back(q, l);
+                    here.emplace_back(q.get(), l);
                     continue;
                 }
                 try {
-                    threads.emplace_back(lane, q, l);
+                    threads.emplace_back(lane, q.get(), l);
                 } catch (const std::system_error&) {
-                    here.emplace_back(q, l);
+                    here.emplace_back(q.get(), l);
                 }
             }
         for (const auto& h : here) lane(h.first, h.second);
@@ -140,7 +153,6 @@ int solve_lanes(cylpoisson_plan* const* plans, const double* const* rho, double*
                     break;
                 }
     }
-    for (Queue* q : queues) delete q;
     (void)hipEventDestroy(start);
     return status;
 }
