@@ -629,11 +629,16 @@ template <typename T, int NU, int KIND, bool ZC, int COEF>
 using PassOf = Pass<T, NU, kind_input(KIND), (KIND >= kDownPro), (KIND != kUp), ZC, COEF>;
 
 // Two wavefronts per SIMD (up to 256 registers) where that spills nothing or
-// little, else one.
-constexpr int pass_waves(int nu, int coef) { return nu <= 3 || (nu == 4 && coef != kSomeRows) ? 2 : 1; }
+// little, else one: the FP64 passes of five and six sweeps, and of four that
+// read their iterate (`zero`: a pass that starts from zero).  Chunks are cut for
+// this many: V(4,4) at 129 x 64 x 129 takes 411 us, and 517 when cut for two.
+template <typename T>
+constexpr int pass_waves(int nu, int coef, bool zero) {
+    return sizeof(T) == 4 || nu <= 3 || (nu == 4 && (coef != kSomeRows || zero)) ? 2 : 1;
+}
 
 template <typename T, int NU, int KIND, bool ZC, int COEF>
-__global__ void __launch_bounds__(64, pass_waves(NU, COEF)) k_pass(PassArgs<T> a) {
+__global__ void __launch_bounds__(64, pass_waves<T>(NU, COEF, KIND == kDownZero)) k_pass(PassArgs<T> a) {
     PassOf<T, NU, KIND, ZC, COEF> pass(a);
     pass.run();
 }
@@ -655,7 +660,7 @@ __global__ void __launch_bounds__(64, 2) k_pass_fine(PassArgs<T> a) {
 // right-hand side are bitwise theirs; the residual norm between the passes is
 // not formed.
 template <typename T, int NU, bool ZC, int COEF>
-__global__ void __launch_bounds__(64, pass_waves(NU, COEF)) k_pass_merge(PassArgs<T> a) {
+__global__ void __launch_bounds__(64, pass_waves<T>(NU, COEF, false)) k_pass_merge(PassArgs<T> a) {
     PassOf<T, NU, kMerge, ZC, COEF> pass(a);
     pass.run();
 }
@@ -674,26 +679,32 @@ Shape pass_shape(const cylpoisson_plan* p, int l, int nu, bool down, bool merge 
     Shape sh;
     sh.nstrips = strips_of(L.v.nr, nu);
     const int outside = L.v.nz - 2 - (L.reg_hi - L.reg_lo);
-    sh.coef = outside <= 0 ? kOneBand : nu >= 4 || outside > kFewRows ? kRowTables : kSomeRows;
+    // other sweep counts than the default's two (four merged) have one form
+    sh.coef = nu != (merge ? 4 : 2) ? kSomeRows
+              : outside <= 0        ? kOneBand
+              : merge || outside > kFewRows ? kRowTables
+                                            : kSomeRows;
     const int rows = L.v.nz - 2;
     int chunk = merge ? p->opt.chunk_rows_merge : l == 0 ? p->opt.chunk_rows : p->opt.chunk_rows_coarse;
     const bool automatic = chunk <= 0;
     // beside other solves fewer; but the finest FP64 up pass leaves the norms'
     // partial sums, whose order must be that of a solve alone
     const int share = l == 0 && !down && sizeof(T) == 8 ? 1 : p->share;
+    // (a coarser level's down pass starts from zero)
+    const int waves = pass_waves<T>(nu, sh.coef, down && !merge && l > 0);
     if (automatic) {
         // as many chunks as keep every wavefront resident at once
-        auto rows_for = [&](int waves) {
-            const int per_plane = std::max(1, waves / (share * p->nt * sh.nstrips));
+        auto rows_for = [&](int n) {
+            const int per_plane = std::max(1, n / (share * p->nt * sh.nstrips));
             return std::max(kMinChunk, (rows + per_plane - 1) / per_plane);
         };
-        chunk = rows_for(kPassWaves * pass_waves(nu, sh.coef) / 2);
+        chunk = rows_for(kPassWaves * waves / 2);
         // A merged chunk of c rows runs c + 19 or so steps.  Where it is short, a
         // second wavefront a SIMD mostly repeats rows of the first: up to
         // kShortChunk rows with one, one it is (151 x 45 x 203, 10 rows or 19: 382
         // and 366 us the solve; 129 x 64 x 129, 8 or 16: 275 and 268; 101 x 64 x 401,
         // 13 or 25: 549 and 546; 400 x 128 x 512, 128 or 255: 2412 and 2522).
-        if (merge && share == 1 && pass_waves(nu, sh.coef) == 2) {
+        if (merge && share == 1 && waves == 2) {
             const int longer = rows_for(kPassWaves / 2);
             if (longer <= kShortChunk) chunk = longer;
         }
