@@ -309,14 +309,24 @@ int plane_pairs(const cylpoisson_plan* p, int g) {
 
 }  // namespace
 
+// Planes up to which this is faster than the passes.  A plane's workgroup fills
+// a compute unit, so that beyond 256 planes they take turns, which the passes do
+// not: with one pair a thread it is faster all the same (17 x 1024 x 17: 2431 us
+// the solve, 2493 by passes; 41 x 1024 x 41: 2574, 2648), with two only up to
+// there (65 x 256 x 65: 303, 329; 65 x 320 x 65: 1052, 996).  With two pairs and the
+// exact solve's tables read from L2 by every plane, up to 64 (72 x 64 x 56: 275,
+// 283; 72 x 96 x 56: 313, 298; 72 x 128 x 56: 358, 307).  The solves beside this
+// one in a batch do not enter: their number must not change a solve's norms.
+int plane_most(int g, int pairs) { return pairs == 1 ? 1 << 30 : g <= kTablesG ? 256 : 64; }
+
 // Merged cycles (without the option "timing", which takes the passes apart) on
 // two levels, the second solved by one workgroup a plane, and
 // a finest plane whose nodes fit a workgroup's registers and LDS.
 bool plane_active(const cylpoisson_plan* p) {
     if (p->opt.timing || direct_level(p) != 1 || !fused_merge_ok(p)) return false;
     const DirectLevel& d = p->dir[p->opt.direct == 2 ? 1 : 0];
-    const int g = direct_g(p->hl[1]);
-    return !d.big && plane_pairs(p, g) <= kMaxPairs && plane_lds(p->dl[0].v, p->dl[1].v, g) <= 150 * 1024;
+    const int g = direct_g(p->hl[1]), pairs = plane_pairs(p, g);
+    return !d.big && pairs <= kMaxPairs && p->nt <= plane_most(g, pairs) && plane_lds(p->dl[0].v, p->dl[1].v, g) <= 150 * 1024;
 }
 
 hipError_t launch_plane(cylpoisson_plan* p, int cycles, bool zero_top, bool pro, double* partial, int partial_ld,
