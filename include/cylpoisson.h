@@ -180,8 +180,9 @@ void cylpoisson_plan_destroy(cylpoisson_plan* plan);
  *                    sweep everywhere (default 1)
  *   "chunk_rows"     axial rows per wavefront of the finest level's fused passes (0 =
  *                    automatic: as many chunks as keep every wavefront resident)
- *   "prefetch"       accepted and read back, without effect: the fused passes load
- *                    two rows ahead of the one they consume (1 .. 3; default 1)
+ *   "prefetch"       accepted and read back; the fused passes load two rows ahead of
+ *                    the one they consume whatever it says, but it counts in the
+ *                    size rule of "precision" 32 (1 .. 3; default 1)
  *   "timing"         1 = record per-kernel-class device times (cylpoisson_stats);
  *                    2 = the finest-level pass classes only (fewer event records
  *                    between the other launches); 0 = off (0 .. 2; default 0).
@@ -205,19 +206,24 @@ void cylpoisson_plan_destroy(cylpoisson_plan* plan);
  *                    run in FP32, with the coarsest solve still in FP64.  Setting
  *                    32 allocates the FP32 level buffers (ENOMEM on failure); it
  *                    needs the fused passes and the LDS bottom kernel on this grid
- *                    (EINVAL otherwise, also at solve time if options changed)
+ *                    (EINVAL otherwise, also at solve time if options changed), and
+ *                    its size rule: every level above the bottom kernel coarsened
+ *                    in r and of at most some number of radial nodes, fewer with
+ *                    more sweeps, a larger "prefetch" or longer chunks (two sweeps:
+ *                    587, 447 with "prefetch" 2 or 3, 483 with "chunk_rows" 256,
+ *                    345 with 512)
  *   "inner_cycles"   FP32 V-cycles per refinement step (1 .. 8; default 2)
  *   "groups"         plane groups whose V-cycles run on separate streams between
  *                    convergence checks (1 .. 8; default 1; used when every level
- *                    above the bottom kernel has fused passes, else 1).  Results
- *                    do not depend on it
+ *                    above the bottom kernel has fused passes and is within the size
+ *                    rule of "precision" 32, else 1).  Results do not depend on it
  *   "warm_start"     1 = cylpoisson_solve takes the phi it is given as the initial
  *                    guess (its interior nodes; boundary nodes are ignored and
  *                    rewritten); 0 = zero initial guess, phi not read (default 0)
  *   "masks"          1 = per-plane convergence masks: a plane whose weighted squared
  *                    residual is within tol^2 ||b||^2 / Ntheta stops being cycled
- *                    (its last iterate is kept), FP64 path with fused passes
- *                    (default 0)
+ *                    (its last iterate is kept), FP64 path with fused passes within
+ *                    the size rule of "precision" 32 (ignored beyond; default 0)
  *   "krylov"         1 = learned solve: flexible GMRES with the attached network
  *                    (cylpoisson_plan_set_net) as right preconditioner, judged
  *                    against one plain V-cycle and replaced by V-cycles when it
@@ -267,7 +273,7 @@ void cylpoisson_plan_destroy(cylpoisson_plan* plan);
  *                    nu1 + nu2 from 4 to 6, at most 513 radial nodes and one
  *                    plane group; captured graphs ("graph") merge the same
  *                    passes (default 1)
- *   "merge_prefetch" accepted and read back, without effect, as "prefetch" (1 .. 2; default 1)
+ *   "merge_prefetch" accepted and read back, without effect (1 .. 2; default 1)
  *   "direct"         exact solve of a coarse level (Sec. 3.3 solves the coarsest one
  *                    directly): the V-cycle stops at that level and solves it on every
  *                    plane with the axial generalised eigenvectors of the level's

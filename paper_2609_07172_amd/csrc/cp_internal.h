@@ -110,7 +110,7 @@ struct Options {
     int fused = 1;
     int chunk_rows = 0;  // rows per wavefront in the finest fused passes (0 = automatic)
     int chunk_rows_coarse = 0;  // the same on the coarser levels
-    int prefetch = 1;    // kept for callers that set it; the passes load two rows ahead
+    int prefetch = 1;    // the passes load two rows ahead; counts in offered_level's size rule only
     int timing = 0;      // record per-kernel-class device times with HIP events
     int bottom = 1;      // run the small levels in one LDS-resident kernel per plane
     int fft = 1;         // azimuthal transforms as register FFTs where Ntheta allows
@@ -129,7 +129,7 @@ struct Options {
     int nu1_coarse = 0, nu2_coarse = 0;  // sweeps on levels >= 1 (0: nu1, nu2)
     int fmg = 0;           // 1: full-multigrid start before the V-cycles
     int merge = 1;         // 1: merged finest pass between cycles without a convergence check
-    int merge_prefetch = 1;  // likewise
+    int merge_prefetch = 1;  // kept for callers that set it
     int chunk_rows_merge = 0;  // axial rows per wavefront of the merged pass (0 = automatic)
     int tune_omega = 0;    // 1: cylpoisson_autotune also picks omega by the measured contraction
     int nn_target = 0;     // training targets: 0 = SOR correction of the residual, 1 = V-cycle iterate error

@@ -417,7 +417,7 @@ namespace {
 // level coarsened in r, whose rows' pipeline of nu sweeps (one to two rows of
 // prefetch) and per-row tables fit in 64 KB of LDS (80 KB on a stretched mesh)
 // in FP64.  The passes no longer need LDS, but what these options accept and
-// refuse stays as it was.
+// refuse stays as it was; the header states the rule, options included.
 bool offered_level(const cylpoisson_plan* p, int l) {
     const DeviceLevel& L = p->dl[l];
     const DeviceLevel& C = p->dl[l + 1];

@@ -1218,8 +1218,9 @@ int solve_impl(cylpoisson_plan* p, const double* rho, double* phi, double tol, v
         return p->stats.status = CYLPOISSON_EINVAL;
     }
     if (mixed && (p->dl32.empty() || !mixed_supported(p))) {
-        set_error("mixed precision needs fused passes on every level above the LDS bottom kernel "
-                  "(check the options fused, bottom, nu1, nu2 and chunk sizes)");
+        set_error("mixed precision needs fused passes on every level above the LDS bottom kernel, each within "
+                  "its size rule (check the options fused, bottom, smoother, nu1, nu2, prefetch, chunk_rows and "
+                  "chunk_rows_coarse against the %d radial nodes)", p->nr);
         return p->stats.status = CYLPOISSON_EINVAL;
     }
     hipStream_t s = static_cast<hipStream_t>(stream);
