@@ -180,9 +180,11 @@ void cylpoisson_plan_destroy(cylpoisson_plan* plan);
  *                    sweep everywhere (default 1)
  *   "chunk_rows"     axial rows per wavefront of the finest level's fused passes (0 =
  *                    automatic: as many chunks as keep every wavefront resident)
- *   "prefetch"       accepted and read back; the fused passes load two rows ahead of
- *                    the one they consume whatever it says, but it counts in the
- *                    size rule of "precision" 32 (1 .. 3; default 1)
+ *   "prefetch"       1 = the first down passes after a full-multigrid start form it
+ *                    as they stream; 2, 3 = it is written out and read back, with
+ *                    the same results.  The fused passes load two rows ahead of the
+ *                    one they consume whatever it says.  Counts in the size rule of
+ *                    "precision" 32 (1 .. 3; default 1)
  *   "timing"         1 = record per-kernel-class device times (cylpoisson_stats);
  *                    2 = the finest-level pass classes only (fewer event records
  *                    between the other launches); 0 = off (0 .. 2; default 0).

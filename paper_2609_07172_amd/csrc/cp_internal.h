@@ -110,7 +110,7 @@ struct Options {
     int fused = 1;
     int chunk_rows = 0;  // rows per wavefront in the finest fused passes (0 = automatic)
     int chunk_rows_coarse = 0;  // the same on the coarser levels
-    int prefetch = 1;    // the passes load two rows ahead; counts in offered_level's size rule only
+    int prefetch = 1;    // 2, 3: a full-multigrid start is written out; counts in offered_level's size rule
     int timing = 0;      // record per-kernel-class device times with HIP events
     int bottom = 1;      // run the small levels in one LDS-resident kernel per plane
     int fft = 1;         // azimuthal transforms as register FFTs where Ntheta allows

@@ -56,10 +56,11 @@ hipError_t fused_down(cylpoisson_plan* p, int l, bool zero_u, bool zero_interior
 // The first down pass on level l after a full-multigrid start, with the
 // start's interpolation from level l + 1 folded in: two or three pre-sweeps,
 // fused passes on level l.  The finest level's first cycle uses it, and so
-// does the start's own V-cycle on level 1.
+// does the start's own V-cycle on level 1.  With "prefetch" 2 or 3 the start is
+// written out and read back instead, which a plan can compare this with.
 bool fused_down_pro_ok(const cylpoisson_plan* p, int l) {
     const int nu = nu_pre(p, l);
-    return fused_supported(p, l) && (nu == 2 || nu == 3);
+    return fused_supported(p, l) && (nu == 2 || nu == 3) && p->opt.prefetch == 1;
 }
 
 hipError_t fused_down_pro(cylpoisson_plan* p, hipStream_t s, int p0, int np, int l) {
