@@ -34,6 +34,9 @@ struct ApplyArgs {
     int units;                     // runs x blocks of rows x strips
 };
 
+// WIDE: rows of hundreds of megabytes, too long for 32-bit offsets within a block
+// of them: a buffer a row from the strip's first column on instead of one a block.
+template <bool WIDE>
 __global__ void __launch_bounds__(64, 2) k_apply(ApplyArgs a) {
 #pragma clang fp contract(off)
     const LevelView& v = a.v;
@@ -48,7 +51,17 @@ __global__ void __launch_bounds__(64, 2) k_apply(ApplyArgs a) {
     const int ja = run * a.run, jb = min(a.nt, ja + a.run);
     const unsigned row8 = (unsigned)(v.pitch * 8);
     const long long left = (long long)(v.nz - s) * v.pitch;
-    const unsigned voff = c1 < v.nr ? (unsigned)c1 * 8 : kOff;
+    const int col0 = WIDE ? 2 * strip * kStripPairs : 0;
+    const unsigned voff = c1 < v.nr ? (unsigned)(c1 - col0) * 8 : kOff;
+    // the buffer of an array's rows from row s on, of which `base` is the first; row y in it
+    auto rows = [&](const double* base) { return make_rsrc(base, left); };
+    auto row = [&](rsrc_t r, const double* base, int y) {
+        if constexpr (WIDE)
+            return make_rsrc(base + (long long)(y - s) * v.pitch + col0, (long long)(v.nz - y) * v.pitch - col0);
+        else
+            return r;
+    };
+    auto offset = [&](int y) { return WIDE ? 0u : (unsigned)(y - s) * row8; };
     const unsigned vst = own && c1 + 1 < v.nr ? voff : kOff;     // whole pairs
     const unsigned vlast = own && c1 == v.nr - 1 ? voff : kOff;  // the last column of an odd count
     double rw[2], re[2], rb[2], rm[2];
@@ -64,14 +77,15 @@ __global__ void __launch_bounds__(64, 2) k_apply(ApplyArgs a) {
     double zc[kRows], zs[kRows], zn[kRows];
     double is[kRows][2];  // 1 / s; zero on the ring
     {
-        const rsrc_t ri = make_rsrc(a.inv_s + (long long)s * v.pitch, left);
+        const double* base = a.inv_s + (long long)s * v.pitch;
+        const rsrc_t ri = rows(base);
 #pragma unroll
         for (int k = 0; k < kRows; ++k) {
             const int y = min(z0 + k, v.nz - 1);
             zc[k] = zct[y];
             zs[k] = zst[y];
             zn[k] = znt[y];
-            const Pair<double> p = load2<double>(ri, voff, (unsigned)(y - s) * row8);
+            const Pair<double> p = load2<double>(row(ri, base, y), voff, offset(y));
             is[k][0] = act[0] && z0 + k <= v.nz - 2 ? p.a : 0.0;
             is[k][1] = act[1] && z0 + k <= v.nz - 2 ? p.b : 0.0;
         }
@@ -79,10 +93,13 @@ __global__ void __launch_bounds__(64, 2) k_apply(ApplyArgs a) {
     // rows z0 - 1 .. z0 + kRows of plane j (rows past the last repeat it)
     auto load = [&](int j, Pair<double> (&o)[kRows + 2]) {
         const int q = j < 0 ? j + a.nt : j >= a.nt ? j - a.nt : j;
-        const rsrc_t r = make_rsrc(a.u + (long long)q * v.pstride + (long long)s * v.pitch, left);
+        const double* base = a.u + (long long)q * v.pstride + (long long)s * v.pitch;
+        const rsrc_t r = rows(base);
 #pragma unroll
-        for (int k = 0; k < kRows + 2; ++k)
-            o[k] = load2<double>(r, voff, (unsigned)(min(z0 - 1 + k, v.nz - 1) - s) * row8);
+        for (int k = 0; k < kRows + 2; ++k) {
+            const int y = min(z0 - 1 + k, v.nz - 1);
+            o[k] = load2<double>(row(r, base, y), voff, offset(y));
+        }
     };
     Pair<double> before[kRows + 2], at[kRows + 2], after[kRows + 2], next[kRows + 2];
     load(ja - 1, before);
@@ -90,7 +107,8 @@ __global__ void __launch_bounds__(64, 2) k_apply(ApplyArgs a) {
     load(ja + 1, after);
     for (int j = ja; j < jb; ++j) {
         if (j + 1 < jb) load(j + 2, next);
-        const rsrc_t ro = make_rsrc(a.out + (long long)j * v.pstride + (long long)s * v.pitch, left);
+        const double* base = a.out + (long long)j * v.pstride + (long long)s * v.pitch;
+        const rsrc_t ro = rows(base);
 #pragma unroll
         for (int k = 0; k < kRows; ++k) {
             const Pair<double> m = at[k + 1];
@@ -102,19 +120,22 @@ __global__ void __launch_bounds__(64, 2) k_apply(ApplyArgs a) {
             const double o0 = fma((rm[0] * zc[k]) * a.dt2, t0, apply_row(m.a, west, m.b, at[k].a, at[k + 2].a, k0));
             const double o1 = fma((rm[1] * zc[k]) * a.dt2, t1, apply_row(m.b, m.a, east, at[k].b, at[k + 2].b, k1));
             if (z0 + k <= v.nz - 2) {
-                const unsigned so = (unsigned)(z0 + k - s) * row8;
-                store2<double>(ro, vst, so, act[0] ? o0 * is[k][0] : 0.0, act[1] ? o1 * is[k][1] : 0.0);
-                store1<double>(ro, vlast, so, 0.0);
+                const rsrc_t r = row(ro, base, z0 + k);
+                const unsigned so = offset(z0 + k);
+                store2<double>(r, vst, so, act[0] ? o0 * is[k][0] : 0.0, act[1] ? o1 * is[k][1] : 0.0);
+                store1<double>(r, vlast, so, 0.0);
             }
         }
         if (z0 == 1) {
-            store2<double>(ro, vst, 0, 0.0, 0.0);
-            store1<double>(ro, vlast, 0, 0.0);
+            const rsrc_t r = row(ro, base, 0);
+            store2<double>(r, vst, 0, 0.0, 0.0);
+            store1<double>(r, vlast, 0, 0.0);
         }
         if (z0 + kRows >= v.nz - 1) {
-            const unsigned so = (unsigned)(v.nz - 1 - s) * row8;
-            store2<double>(ro, vst, so, 0.0, 0.0);
-            store1<double>(ro, vlast, so, 0.0);
+            const rsrc_t r = row(ro, base, v.nz - 1);
+            const unsigned so = offset(v.nz - 1);
+            store2<double>(r, vst, so, 0.0, 0.0);
+            store1<double>(r, vlast, so, 0.0);
         }
 #pragma unroll
         for (int k = 0; k < kRows + 2; ++k) {
@@ -129,8 +150,6 @@ __global__ void __launch_bounds__(64, 2) k_apply(ApplyArgs a) {
 
 hipError_t launch_apply(const DeviceLevel& L, int nt, double dtheta, const double* u, const double* inv_s, double* out,
                         hipStream_t s) {
-    // 32-bit byte offsets within a block of rows
-    if ((kRows + 2LL) * L.v.pitch * 8 > kMaxRange) return hipErrorInvalidValue;
     ApplyArgs a{};
     a.v = L.v;
     a.u = u;
@@ -146,7 +165,11 @@ hipError_t launch_apply(const DeviceLevel& L, int nt, double dtheta, const doubl
     a.run = std::min(nt, std::max(kMinRun, (nt + want - 1) / want));
     a.nruns = (nt + a.run - 1) / a.run;
     a.units = (int)(tiles * a.nruns);
-    k_apply<<<8 * ((a.units + 7) / 8), 64, 0, s>>>(a);
+    const int blocks = 8 * ((a.units + 7) / 8);
+    if ((kRows + 2LL) * L.v.pitch * 8 <= kMaxRange)  // 32-bit byte offsets within a block of rows
+        k_apply<false><<<blocks, 64, 0, s>>>(a);
+    else
+        k_apply<true><<<blocks, 64, 0, s>>>(a);
     return hipGetLastError();
 }
 

@@ -27,8 +27,9 @@ struct RowShape {
     int bs;                       // of them side by side (a wavefront takes every bs-th strip)
 };
 
-// `most`: wavefronts per plane at most (one partial sum each)
-RowShape row_shape(int rows, int nr, long long pitch, int nt, int most) {
+// `most`: wavefronts per plane at most (one partial sum each); `wide`: rows too
+// long for offsets within a chunk
+RowShape row_shape(int rows, int nr, long long pitch, int nt, int most, bool wide = false) {
     RowShape s;
     const int pairs = (nr - 1) / 2 + 1;
     s.nstrips = pairs <= 64 ? 1 : (pairs - 2 + kStripPairs - 1) / kStripPairs;
@@ -38,10 +39,10 @@ RowShape row_shape(int rows, int nr, long long pitch, int nt, int most) {
     s.chunk = std::max(kMinChunk, (rows + want - 1) / want);
     s.chunk = std::max(s.chunk, (rows + most / s.bs - 1) / (most / s.bs));
     // 32-bit byte offsets within a chunk
-    s.chunk = (int)std::max(1LL, std::min<long long>(s.chunk, kMaxRange / (pitch * 8) - 2 * kAhead));
+    if (!wide) s.chunk = (int)std::max(1LL, std::min<long long>(s.chunk, kMaxRange / (pitch * 8) - 2 * kAhead));
     s.nchunks = (rows + s.chunk - 1) / s.chunk;
     s.nb = s.nchunks * s.bs;
-    s.ok = s.nb <= most && (s.chunk + 2LL) * pitch * 8 <= kMaxRange;
+    s.ok = s.nb <= most && (wide || (s.chunk + 2LL) * pitch * 8 <= kMaxRange);
     return s;
 }
 
@@ -108,9 +109,12 @@ enum RowMode { kNormX, kNormR, kNormB, kNormBoth, kRefineZero, kRefineAsIs, kRef
 // sharing rows through LDS, a barrier a row).  At 129 x 64 x 129, where launches
 // count, kNormBoth and its sums take 9 + 3 us for what were a residual written
 // and read again and three sums (37 us).
-template <int MODE>
+// WIDE (norms only): rows of hundreds of megabytes, whose loads take a buffer a
+// row from the strip's first column on instead of one a chunk.
+template <int MODE, bool WIDE>
 __global__ void __launch_bounds__(64, 4) k_rows(RowArgs a) {
 #pragma clang fp contract(off)
+    static_assert(!WIDE || MODE <= kNormBoth, "the wide form stores nothing");
     constexpr bool RING = MODE == kNormB || MODE == kRefineZero;  // reads u's ring only
     constexpr bool U = MODE != kNormX;
     constexpr bool R = U && MODE != kNormB;
@@ -139,20 +143,29 @@ __global__ void __launch_bounds__(64, 4) k_rows(RowArgs a) {
         w.columns(a.sh, v, strip);
         const int c1 = w.c1;
         const bool a0 = w.act[0], a1 = w.act[1], any = a0 || a1;
-        const unsigned voff = c1 < v.nr ? (unsigned)c1 * 8 : kOff;
+        const int col0 = WIDE ? 2 * strip * kStripPairs : 0;
+        const unsigned voff = c1 < v.nr ? (unsigned)(c1 - col0) * 8 : kOff;
         const unsigned vring = a0 && a1 ? kOff : voff;
         const unsigned vin = any ? voff : kOff, vin4 = any ? (unsigned)c1 * 4 : kOff;
         const unsigned vst = w.own ? vin : kOff, vst4 = w.own ? vin4 : kOff;
+        // row xr, in the buffer `r` of the rows from `base` on
+        auto load_row = [&](rsrc_t r, const double* base, unsigned off, int xr) {
+            if constexpr (WIDE)
+                return load2<double>(make_rsrc(base + (long long)(xr - s) * v.pitch + col0,
+                                               (long long)(v.nz - xr) * v.pitch - col0), off, 0);
+            else
+                return load2<double>(r, off, (unsigned)(xr - s) * row8);
+        };
         auto load_u = [&](int x) -> Pair<double> {
             if (!U) return {0.0, 0.0};
             const int xr = min(x, zb);
-            return load2<double>(ru, RING && xr >= 1 && xr <= v.nz - 2 ? vring : voff, (unsigned)(xr - s) * row8);
+            return load_row(ru, a.u + first, RING && xr >= 1 && xr <= v.nz - 2 ? vring : voff, xr);
         };
         auto load_e = [&](int x) -> Pair<float> {
             const int xr = min(x, zb);
             return load2<float>(re, xr >= 1 && xr <= v.nz - 2 ? vin4 : kOff, (unsigned)(xr - s) * row4);
         };
-        auto load_f = [&](int x) { return load2<double>(rf, vin, (unsigned)(min(x, zb) - s) * row8); };
+        auto load_f = [&](int x) { return load_row(rf, a.f + first, vin, min(x, zb)); };
         // the iterate of a loaded row
         auto value = [&](int x, const Pair<double>& l, const Pair<float>& d, double (&o)[2]) {
             const bool in = x >= 1 && x <= v.nz - 2;
@@ -396,9 +409,15 @@ __global__ void __launch_bounds__(64) k_norm_final(const double* __restrict__ pa
 }
 
 template <int MODE>
-hipError_t launch_rows(RowArgs& a, int nt, hipStream_t s) {
-    if (!a.sh.ok) return hipErrorInvalidValue;
-    k_rows<MODE><<<dim3(a.sh.nb, nt), 64, 0, s>>>(a);
+hipError_t launch_rows(RowArgs& a, int nt, int most, hipStream_t s) {
+    if constexpr (MODE <= kNormBoth)
+        if (!a.sh.ok) {
+            a.sh = row_shape(a.v.nz - 2, a.v.nr, a.v.pitch, nt, most, true);
+            k_rows<MODE, true><<<dim3(a.sh.nb, nt), 64, 0, s>>>(a);
+            return hipGetLastError();
+        }
+    if (!a.sh.ok) return hipErrorInvalidValue;  // (the refinement: fused levels only, whose rows are short)
+    k_rows<MODE, false><<<dim3(a.sh.nb, nt), 64, 0, s>>>(a);
     return hipGetLastError();
 }
 
@@ -422,21 +441,22 @@ hipError_t launch_plane_norms(const DeviceLevel& L, int nt, const double* x, dou
     RowArgs a = row_args(L, nt, nullptr, kMaxPartial);
     a.f = x;
     a.partial = partial;
-    const hipError_t e = launch_rows<kNormX>(a, nt, s);
+    const hipError_t e = launch_rows<kNormX>(a, nt, kMaxPartial, s);
     return e != hipSuccess ? e : launch_norm_final(partial, a.sh.nb, nt, norms_out, s);
 }
 
 hipError_t launch_norms(const DeviceLevel& L, int nt, const double* lam, const double* u, const double* f,
                         double* partial, double* r_norms, double* b_norms, hipStream_t s) {
     const bool both = r_norms && b_norms;
-    RowArgs a = row_args(L, nt, lam, both ? kMaxPartial / 2 : kMaxPartial);
+    const int most = both ? kMaxPartial / 2 : kMaxPartial;
+    RowArgs a = row_args(L, nt, lam, most);
     a.u = u;
     a.f = f;
     a.partial = partial;
     a.partial2 = both ? partial + kMaxPartial / 2 : partial;
-    const hipError_t e = both      ? launch_rows<kNormBoth>(a, nt, s)
-                         : r_norms ? launch_rows<kNormR>(a, nt, s)
-                                   : launch_rows<kNormB>(a, nt, s);
+    const hipError_t e = both      ? launch_rows<kNormBoth>(a, nt, most, s)
+                         : r_norms ? launch_rows<kNormR>(a, nt, most, s)
+                                   : launch_rows<kNormB>(a, nt, most, s);
     if (e != hipSuccess) return e;
     k_norm_final<<<nt, 64, 0, s>>>(partial, a.sh.nb, kMaxPartial / 2, r_norms ? r_norms : b_norms,
                                    both ? b_norms : nullptr);
@@ -480,9 +500,9 @@ hipError_t launch_refine(const DeviceLevel& L, int nt, const double* lam, const 
     a.r32 = r32;
     a.partial = partial;
     if (e && uin == uout) return hipErrorInvalidValue;
-    const hipError_t err = e      ? launch_rows<kRefineAdd>(a, nt, s)
-                           : uout ? launch_rows<kRefineZero>(a, nt, s)
-                                  : launch_rows<kRefineAsIs>(a, nt, s);
+    const hipError_t err = e      ? launch_rows<kRefineAdd>(a, nt, kMaxPartial, s)
+                           : uout ? launch_rows<kRefineZero>(a, nt, kMaxPartial, s)
+                                  : launch_rows<kRefineAsIs>(a, nt, kMaxPartial, s);
     return err != hipSuccess ? err : launch_norm_final(partial, a.sh.nb, nt, norms_out, s);
 }
 
