@@ -1,7 +1,9 @@
 // Fused streaming multigrid passes, FP64, for sweep counts other than the
 // default's (one, three and four sweeps; five and six merged).  One
 // instantiation serves every level: rows outside the regular band form their
-// coefficients from the tables.
+// coefficients from the tables, on a stretched mesh all of them (400 x 128 x 512
+// cells stretched 4:1, V(3,3): 1.32 ms a cycle, 3.2 as one workgroup per plane
+// and chunk).
 #include "fused_pass.h"
 
 namespace cp {

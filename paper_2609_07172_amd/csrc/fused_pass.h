@@ -31,9 +31,9 @@
 // plane and chunk with rows exchanged through LDS, a barrier and several LDS
 // round trips per row, at one wavefront per SIMD), the up pass 159 us (160),
 // the first down pass 144 us (169).  On small grids the chain of dependent
-// operations of one step times the rows of a chunk bounds it: 13.6 us merged
-// at 33 x 16 x 33 (56 us: 64-row chunks, and unrolled code that was fetched once
-// per step), 24 us at 129 x 64 x 129 (85 us).
+// operations of one step times the rows of a chunk bounds it: 21 us merged at
+// 129 x 64 x 129 (85 us: 64-row chunks, and unrolled code that was fetched once per
+// step).
 //
 // Coarsening keeps every even node (and the last one), in z always 2:1 or not
 // at all (ZC), in r likewise (args.rc), so a fine column or row 2I lies on the
