@@ -240,13 +240,15 @@ hipError_t vcycle(cylpoisson_plan* p, int l, hipStream_t s, bool zero_top, int s
     DeviceLevel& L = p->dl[l];
     hipError_t e = hipSuccess;
     if (l > 0 && l == direct_level(p)) return launch_direct(p, s, p0, np);
+    // (before the coarsest level's kernels, which serve all planes: the bottom
+    // kernel may start there, and other streams have the other planes)
+    if (l > 0 && l == p->bottom_level && bottom_active(p)) return launch_bottom(p, s, p0, np);
     if (l == nl - 1) {
         if (l > 0) e = launch_zero_interior(L, p->nt, L.u, s);
         if (e == hipSuccess)
             e = launch_coarse_solve(L, p->nt, p->d_lam, p->d_cinv, p->coarse_n, L.f, L.u, s);
         return e;
     }
-    if (l > 0 && l == p->bottom_level && bottom_active(p)) return launch_bottom(p, s, p0, np);
     DeviceLevel& C = p->dl[l + 1];
     if (l == 0 && fused_supported(p, 0)) {
         hipError_t e = cycle_down(p, s, zero_top, pro, p0, np);
