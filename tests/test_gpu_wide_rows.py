@@ -70,3 +70,5 @@ def test_same_as_at_an_ordinary_pitch(pitch):
     assert torch.isfinite(out[0][0]).all() and (out[0][0] == out[1][0]).all()
     # the order of the sums differs with the shape: 64 bits' rounding of 3000 terms
     assert torch.allclose(out[0][1], out[1][1], rtol=3000 * 2.3e-16, atol=0)
+    del ub, fb, sb, ob, ov
+    torch.cuda.empty_cache()  # tens of gigabytes
